@@ -108,7 +108,11 @@ struct ffpic_ctx {
     int fused_rows = 0;                       // slab height (0 = from fused_slots)
     int push_ppt = 16;                        // FP32 push: particles per thread (8, 16, 32)
     int fused_slots = 0;                      // workgroups resident on the GPU at once
-    void *fz_rowc = nullptr, *fz_colc = nullptr;   // FP32 field step: row / column coefficients
+    // FP32 field step: row / column coefficients; FP64, for the push: logarithms
+    // (fz_rowc) and sines and cosines at multiples of sct_dth (fz_colc), with
+    // their rounding errors
+    void *fz_rowc = nullptr, *fz_colc = nullptr;
+    double sct_dth = 0;
     int device = 0;                           // HIP device the context was created on
     size_t cstride = 0;                       // elements between the components of a field
     std::vector<double> hE0[3], hB0[3];       // FP64 background (host)

@@ -883,6 +883,39 @@ int ffpic_create(const ffpic_desc *d, void *stream, ffpic_ctx **out) {
             upload_field(c, c->B[k], F[3 + k]);
             upload_field(c, c->B0[k], F[3 + k]);
         }
+        if (c->fp64) {
+            // FP64 push: sin and cos of the polar nodes with the rounding
+            // errors of both; where dth exceeds 1/16 of angles that divide
+            // each cell evenly to at most that
+            const int m = (int)std::ceil(16.0 * c->dth);
+            const size_t n = (size_t)c->nth * m + 1;
+            c->sct_dth = m == 1 ? c->dth : c->dth / m;
+            std::vector<double> sct(4 * n);
+            for (size_t j = 0; j < n; j++) {
+                const double t = (double)j * c->sct_dth;
+                const bool pole = j == 0;
+                const double sn = pole ? 0.0 : std::sin(t), cn = pole ? 1.0 : std::cos(t);
+                sct[4 * j] = sn;
+                sct[4 * j + 1] = cn;
+                sct[4 * j + 2] = pole ? 0.0 : (double)(sinl((long double)t) - sn);
+                sct[4 * j + 3] = pole ? 0.0 : (double)(cosl((long double)t) - cn);
+            }
+            // its logarithm on coarse grids: ln 2 (the first part of 32 bits)
+            // and log(1 + k/16), in two parts each
+            std::vector<double> lct(2 * 18);
+            const long double ln2 = logl(2.0L);
+            lct[0] = std::ldexp((double)std::floor(std::ldexp(ln2, 32)), -32);
+            lct[1] = (double)(ln2 - lct[0]);
+            for (int k = 0; k <= 16; k++) {
+                const long double l = logl(1.0L + k / 16.0L);
+                lct[2 * (k + 1)] = (double)l;
+                lct[2 * (k + 1) + 1] = (double)(l - lct[2 * (k + 1)]);
+            }
+            c->fz_rowc = dmalloc(lct.size() * sizeof(double));
+            HCHK(hipMemcpy(c->fz_rowc, lct.data(), lct.size() * sizeof(double), hipMemcpyHostToDevice));
+            c->fz_colc = dmalloc(sct.size() * sizeof(double));
+            HCHK(hipMemcpy(c->fz_colc, sct.data(), sct.size() * sizeof(double), hipMemcpyHostToDevice));
+        }
         if (!c->fp64) {
             alloc3(c, c->dE, true);
             alloc3(c, c->dB, true);
