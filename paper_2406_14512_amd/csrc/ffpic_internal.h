@@ -131,9 +131,11 @@ struct ffpic_ctx {
     // species and their exclusive scan
     int32_t *pair_cnt = nullptr, *pair_off = nullptr;
     int64_t pair_blocks = 0;                  // capacity of pair_cnt (entries - 1)
-    // spectra: table of ln F of the synchrotron function, the gamma bin
-    // edges and frequencies of the last request
-    double *spec_tab = nullptr, *spec_edge = nullptr, *spec_nu = nullptr;
+    // spectra: table of the synchrotron function F and its first entry, the
+    // gamma bin edges and frequencies of the last request (device and host)
+    double *spec_tab = nullptr, *spec_edge = nullptr;
+    double spec_f0 = 0;
+    std::vector<double> spec_host;
     double *psi = nullptr;
     void *f = nullptr;
     uint8_t *kill = nullptr;
@@ -224,10 +226,11 @@ void gauss(ffpic_ctx *c, double *qn, double *dev_map, double *part);
 void divb(ffpic_ctx *c, double *dev_map, double *part);
 void poynting(ffpic_ctx *c, double *dev_L);
 void energies(ffpic_ctx *c, double *part, double *dev_out2);
+void final_max(ffpic_ctx *c, const double *part, double *dev_out);
 // device scratch of one diagnostics call
 struct DiagBufs {
     double *part = nullptr;   // diag_partials() * 5
-    double *out = nullptr;    // 16 result slots
+    double *out = nullptr;    // 32 result slots
     double *qn = nullptr;     // nn node charges (residuals only)
     double *L = nullptr;      // nr + 1 (Poynting flux only)
 };

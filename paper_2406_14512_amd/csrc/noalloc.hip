@@ -64,9 +64,9 @@ extern "C" int ffpic_diagnostics_noalloc(ffpic_ctx *c, uint32_t what, ffpic_diag
         c->last_error = "ffpic_diagnostics_noalloc: the context's device is not the current device";
         return FFPIC_EINVAL;
     }
-    // layout: partials | 16 result slots | L (nr + 1) | node charges (nn)
+    // layout: partials | 32 result slots | L (nr + 1) | node charges (nn)
     const size_t o_out = align256((size_t)diag_partials() * 5 * sizeof(double));
-    const size_t o_L = o_out + align256(16 * sizeof(double));
+    const size_t o_L = o_out + align256(32 * sizeof(double));
     const size_t o_qn = o_L + align256((size_t)(c->nr + 1) * sizeof(double));
     const size_t need = (what & FFPIC_DIAG_RESIDUALS) ? o_qn + c->nn * sizeof(double) : o_qn;
     if (need > kScratchBytes) {

@@ -416,7 +416,7 @@ void free_all(ffpic_ctx *c) {
     for (int s = 0; s < FFPIC_MAX_SPECIES; s++) F(c->perm[s]);
     F(c->inj_rate); F(c->inj_cnt); F(c->inj_off); F(c->nsorted);
     F(c->gj_target); F(c->gj_have); F(c->pair_cnt); F(c->pair_off);
-    F(c->spec_tab); F(c->spec_edge); F(c->spec_nu);
+    F(c->spec_tab); F(c->spec_edge);
     F(c->nslots); F(c->nalive); F(c->removed); F(c->err); F(c->red);
     for (auto &e : c->ev)
         if (e) (void)hipEventDestroy(e);
@@ -704,55 +704,46 @@ void run_cycle_graph(ffpic_ctx *c, int k) {
 
 namespace ffpic {
 
-static double host_max(ffpic_ctx *c, const double *part) {
-    double h[1024];
-    const int n = diag_partials();
-    if (n > 1024) throw Fail{FFPIC_EINVAL, "too many partials"};
-    HCHK(hipMemcpyAsync(h, part, n * sizeof(double), hipMemcpyDeviceToHost, c->stream));
-    HCHK(hipStreamSynchronize(c->stream));
-    double m = 0.0;
-    for (int k = 0; k < n; k++) m = h[k] > m ? h[k] : m;
-    return m;
-}
-
 void run_diagnostics(ffpic_ctx *c, uint32_t what, ffpic_diag *out, double *L, const DiagBufs &b) {
     std::memset(out, 0, sizeof(*out));
     out->step = c->step;
-    HCHK(hipStreamSynchronize(c->stream));
-    unsigned long long rem[FFPIC_MAX_SPECIES * 4];
-    HCHK(hipMemcpy(rem, c->removed, sizeof(rem), hipMemcpyDeviceToHost));
-    HCHK(hipMemcpy(&out->error_word, c->err, sizeof(uint32_t), hipMemcpyDeviceToHost));
-    for (int s = 0; s < c->d.nspec; s++)
-        for (int k = 0; k < 4; k++) out->removed[s][k] = (int64_t)rem[4 * s + k];
-    if (what & FFPIC_DIAG_MOMENTS) {
-        for (int s = 0; s < c->d.nspec; s++) {
-            moments(c, s, b.part, b.out);
-            double h[5];
-            HCHK(hipMemcpyAsync(h, b.out, sizeof(h), hipMemcpyDeviceToHost, c->stream));
-            HCHK(hipStreamSynchronize(c->stream));
-            out->alive[s] = (int64_t)h[0];
-            out->sum_gamma[s] = h[1];
-            for (int k = 0; k < 3; k++) out->sum_u[s][k] = h[2 + k];
-        }
-    }
-    if (what & FFPIC_DIAG_ENERGY) {
-        energies(c, b.part, b.out);
-        double h[2];
-        HCHK(hipMemcpyAsync(h, b.out, sizeof(h), hipMemcpyDeviceToHost, c->stream));
-        HCHK(hipStreamSynchronize(c->stream));
-        out->energy_e = h[0];
-        out->energy_b = h[1];
-    }
+    // every reduction is queued before the first result is read back: out
+    // slots 5 s (moments of species s), 20 (energies), 22, 23 (residuals)
+    constexpr int kOut = 24;
+    if (what & FFPIC_DIAG_MOMENTS)
+        for (int s = 0; s < c->d.nspec; s++) moments(c, s, b.part, b.out + 5 * s);
+    if (what & FFPIC_DIAG_ENERGY) energies(c, b.part, b.out + 20);
     if (what & FFPIC_DIAG_RESIDUALS) {
         gauss(c, b.qn, nullptr, b.part);
-        out->gauss_max = host_max(c, b.part);
+        final_max(c, b.part, b.out + 22);
         divb(c, nullptr, b.part);
-        out->divb_max = host_max(c, b.part);
+        final_max(c, b.part, b.out + 23);
     }
-    if ((what & FFPIC_DIAG_POYNTING) && L) {
-        poynting(c, b.L);
+    const bool flux = (what & FFPIC_DIAG_POYNTING) && L;
+    if (flux) poynting(c, b.L);
+    unsigned long long rem[FFPIC_MAX_SPECIES * 4];
+    double h[kOut];
+    HCHK(hipMemcpyAsync(rem, c->removed, sizeof(rem), hipMemcpyDeviceToHost, c->stream));
+    HCHK(hipMemcpyAsync(&out->error_word, c->err, sizeof(uint32_t), hipMemcpyDeviceToHost, c->stream));
+    HCHK(hipMemcpyAsync(h, b.out, sizeof(h), hipMemcpyDeviceToHost, c->stream));
+    if (flux)
         HCHK(hipMemcpyAsync(L, b.L, (c->nr + 1) * sizeof(double), hipMemcpyDeviceToHost, c->stream));
-        HCHK(hipStreamSynchronize(c->stream));
+    HCHK(hipStreamSynchronize(c->stream));
+    for (int s = 0; s < c->d.nspec; s++)
+        for (int k = 0; k < 4; k++) out->removed[s][k] = (int64_t)rem[4 * s + k];
+    if (what & FFPIC_DIAG_MOMENTS)
+        for (int s = 0; s < c->d.nspec; s++) {
+            out->alive[s] = (int64_t)h[5 * s];
+            out->sum_gamma[s] = h[5 * s + 1];
+            for (int k = 0; k < 3; k++) out->sum_u[s][k] = h[5 * s + 2 + k];
+        }
+    if (what & FFPIC_DIAG_ENERGY) {
+        out->energy_e = h[20];
+        out->energy_b = h[21];
+    }
+    if (what & FFPIC_DIAG_RESIDUALS) {
+        out->gauss_max = h[22];
+        out->divb_max = h[23];
     }
 }
 
@@ -1135,10 +1126,7 @@ int ffpic_get_field(ffpic_ctx *c, int comp, double *dst, int on_dev) {
         case FFPIC_PSI: HCHK(hipMemcpyAsync(d, c->psi, c->nn * sizeof(double), hipMemcpyDeviceToDevice, c->stream)); break;
         case FFPIC_F: to_f64(c, c->f, d, c->nn); break;
         case FFPIC_GAUSS: {
-            double *qn = (double *)dmalloc(c->nn * sizeof(double));
-            gauss(c, qn, d, nullptr);
-            HCHK(hipStreamSynchronize(c->stream));
-            HCHK(hipFree(qn));
+            gauss(c, (double *)c->stAlt[0], d, nullptr);   // scratch as in the diagnostics
             break;
         }
         case FFPIC_DIVB: divb(c, d, nullptr); break;
@@ -1268,18 +1256,17 @@ int ffpic_diagnostics(ffpic_ctx *c, uint32_t what, ffpic_diag *out, double *L) {
     return guarded(c, [&] {
         check_ctx(c);
         if (!out) throw Fail{FFPIC_EINVAL, "NULL output"};
-        struct Owned {   // per-call device scratch, released on every path
-            std::vector<void *> p;
-            ~Owned() { for (void *q : p) (void)hipFree(q); }
-            double *take(size_t n) { p.push_back(dmalloc(n * sizeof(double))); return (double *)p.back(); }
-        } own;
+        // scratch: the partial sums and result slots in the reduction buffer;
+        // the node charges and L(r) in the field step's second state buffers,
+        // which hold nothing between steps (the next step writes all of both
+        // before it reads them): nn doubles, and nr + 1, fit three components
+        // of either precision
         DiagBufs b;
         b.part = c->red;
-        b.out = own.take(16);
-        if (what & FFPIC_DIAG_RESIDUALS) b.qn = own.take(c->nn);
-        if ((what & FFPIC_DIAG_POYNTING) && L) b.L = own.take(c->nr + 1);
+        b.out = c->red + (c->red_len - 32);
+        b.qn = (double *)c->stAlt[0];
+        b.L = (double *)c->stAlt[3];
         run_diagnostics(c, what, out, L, b);
-        HCHK(hipStreamSynchronize(c->stream));
     });
 }
 
