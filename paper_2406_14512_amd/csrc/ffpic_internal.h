@@ -283,7 +283,9 @@ int push_group_slots(int key);
 void push_group_launch(hipStream_t st, int key, const void *jobs, const int *starts, int njobs,
                        int grid, int *ctr);
 size_t field_job_bytes();
-int field_job(ffpic_ctx *c, void *out, int *key); // key: kernel instance, 0..7
+// key: kernel instance, 0..7; rows: slab height of a system without a setting
+int field_job(ffpic_ctx *c, void *out, int *key, int rows);
+int field_strips(const ffpic_ctx *c);             // theta strips of its field step
 int field_group_slots(int key);
 void field_group_launch(hipStream_t st, int key, const void *jobs, const int *starts, int njobs,
                         int grid, int *ctr);

@@ -442,14 +442,21 @@ __global__ void __launch_bounds__(kFzT) k_field_fused(const FusedArgs<R> A) {
     }
 }
 
-// slab height: enough slabs that the grid fills the GPU once, at least 32
-// rows each (the halo costs 6 rows per slab)
-inline int fused_rows(const ffpic_ctx *c) {
+// Slab height: enough slabs that the grid fills the GPU once.  The rows of a
+// slab are a serial chain (1.6 us a row in FP32, 3.9 in FP64 with the
+// force-free stages), so a grid that cannot fill the GPU takes slabs as low as
+// one row: the six halo rows of each then cost idle CUs, not time.  Step
+// without particles, slabs of at least 32 rows against these: 128^2 FP64 151
+// -> 34 us, 300 x 517 FP32 90 -> 39, 1024^2 FP32 120 -> 78, FP64 215 -> 138;
+// from 2048^2 on 32 rows or more fill the GPU.  `shared`: the height for a
+// launch that many systems share (0 = this system alone).
+inline int fused_rows(const ffpic_ctx *c, int shared = 0) {
+    if (c->fused_rows > 0) return c->fused_rows;
+    if (shared > 0) return shared;
     const int nbx = (c->nth + 1 + kFzW - 1) / kFzW;
     const int slots = c->fused_slots > 0 ? c->fused_slots : 768;
     const int slabs = std::max(1, slots / nbx);
-    const int rows = (c->nr + 1 + slabs - 1) / slabs;
-    return c->fused_rows > 0 ? c->fused_rows : std::max(32, rows);
+    return (c->nr + 1 + slabs - 1) / slabs;
 }
 
 // FP64 field step (E and B evolved directly)

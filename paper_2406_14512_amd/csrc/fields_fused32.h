@@ -536,7 +536,7 @@ static int occupancy_slots(const void *kern, int threads, int fallback_per_cu) {
 
 // the arguments of a context's FP32 field step, and the buffer swaps that
 // follow its launch
-static F32Args f32_args(ffpic_ctx *c) {
+static F32Args f32_args(ffpic_ctx *c, int shared_rows = 0) {
     F32Args A{};
     A.nr = c->nr; A.nth = c->nth; A.ld = c->ld;
     A.absorb0 = c->absorb_row0;
@@ -562,7 +562,7 @@ static F32Args f32_args(ffpic_ctx *c) {
     A.colc = (const float4 *)c->fz_colc;
     if (c->fused_slots == 0)
         c->fused_slots = occupancy_slots((const void *)f32_kern(f32_key(c, A)), kFzT, 3);
-    A.rows = fused_rows(c);
+    A.rows = fused_rows(c, shared_rows);
     return A;
 }
 

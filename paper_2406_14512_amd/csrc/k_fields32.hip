@@ -65,11 +65,13 @@ void psi_mask32(ffpic_ctx *c) { run_psi_mask<float>(c); }
 
 size_t field_job_bytes() { return sizeof(F32Job); }
 
-int field_job(ffpic_ctx *c, void *out, int *key) {
+int field_strips(const ffpic_ctx *c) { return (c->nth + 1 + kFzW - 1) / kFzW; }
+
+int field_job(ffpic_ctx *c, void *out, int *key, int rows) {
     F32Job J;
-    J.A = f32_args(c);
+    J.A = f32_args(c, rows);
     J.rowc = (const float4 *)c->fz_rowc;
-    J.strips = (c->nth + 1 + kFzW - 1) / kFzW;
+    J.strips = field_strips(c);
     const int slabs = (c->nr + 1 + J.A.rows - 1) / J.A.rows;
     *key = f32_key(c, J.A);
     std::memcpy(out, &J, sizeof(J));
