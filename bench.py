@@ -41,7 +41,8 @@ COUNTER_FILE = {1: "profiles/k_push32_sheet4096_hbm_counters.txt",
                 0: "profiles/k_push64_sheet4096_hbm_counters.txt"}
 KERNEL_SOURCES = {1: ["paper_2406_14512_amd/csrc/k_push32.hip"],
                   0: ["paper_2406_14512_amd/csrc/k_push64.hip",
-                      "paper_2406_14512_amd/csrc/gather.h"]}
+                      "paper_2406_14512_amd/csrc/gather.h",
+                      "paper_2406_14512_amd/csrc/math64.h"]}
 # headers whose device code the push kernels compile in (the context struct
 # of ffpic_internal.h is host-side bookkeeping, left out)
 COMMON_SOURCES = ["paper_2406_14512_amd/csrc/device_common.h",

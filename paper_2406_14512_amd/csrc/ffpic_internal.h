@@ -108,10 +108,10 @@ struct ffpic_ctx {
     int fused_rows = 0;                       // slab height (0 = from fused_slots)
     int push_ppt = 16;                        // FP32 push: particles per thread (8, 16, 32)
     int fused_slots = 0;                      // workgroups resident on the GPU at once
-    // FP32 field step: row / column coefficients; FP64, for the push: logarithms
-    // (fz_rowc) and sines and cosines at multiples of sct_dth (fz_colc), with
-    // their rounding errors
-    void *fz_rowc = nullptr, *fz_colc = nullptr;
+    // FP32: row / column coefficients of the field step.  FP64 (one allocation,
+    // fz_colc): for the push, sines and cosines at multiples of sct_dth with
+    // their rounding errors; the field step's row blocks; logarithms
+    void *fz_rowc = nullptr, *fz_colc = nullptr, *fz_row64 = nullptr, *fz_log64 = nullptr;
     double sct_dth = 0;
     int device = 0;                           // HIP device the context was created on
     size_t cstride = 0;                       // elements between the components of a field
@@ -240,6 +240,7 @@ void run_diagnostics(ffpic_ctx *c, uint32_t what, ffpic_diag *out, double *L_of_
                      const DiagBufs &b);
 // the same, returning a status (and setting the context's error message)
 // instead of throwing
+std::vector<double> fused64_table(const ffpic_ctx *c);   // row coefficients of the FP64 field step
 void fused32_tables(const ffpic_ctx *c, std::vector<float> &rowc, std::vector<float> &colc);
 int run_diagnostics_checked(ffpic_ctx *c, uint32_t what, ffpic_diag *out, double *L_of_r,
                             const DiagBufs &b);

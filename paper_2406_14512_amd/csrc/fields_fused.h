@@ -44,6 +44,16 @@
 // state is double-buffered (read one buffer, write the other), and so are
 // the deposit accumulators: this step reads the push's and clears the
 // other set for the next push.
+//
+// What bounds it.  A row is a serial chain of about 580 vector instructions
+// per wave, and registers and LDS allow two workgroups per CU, so nothing
+// else hides the latency of its loads: row q + 1 is therefore in flight while
+// row q is worked on, the barriers wait for LDS alone, and the row's geometry
+// comes through the scalar cache.  With the divisions by products of geometry
+// factors taken as products of stored reciprocals, corrected to the rounded
+// quotient, the FP64 step with the force-free stages went from 380 to 206 us
+// at 2048^2 (152 B per node: 3.1 TB/s), from 138 to 77 us at 1024^2; the
+// reciprocals without the loads ahead gave 362 and 119 us.
 #pragma once
 
 #include <algorithm>
@@ -57,9 +67,24 @@ constexpr int kFzT = 256;                 // threads = columns of a strip with i
 constexpr int kFzL = 2, kFzR = 4;         // halo columns before and after
 constexpr int kFzW = kFzT - kFzL - kFzR;  // owned columns per strip
 
-template <typename R>
+// Geometry of one row as the stages read it, in one block of scalar loads: the
+// factors and the reciprocals of those that are divided by (index 0 of the
+// first differences and index nr of the half-cell ones are unused).
+struct FusedRow {
+    // primal: r_i, r_{i+1}, their difference, r_i^2 and (r_{i+1}^2 - r_i^2) / 2
+    double rn, rn1, drn, rn2, y_rn2, dr2n, y_dr2n, pad;
+    // dual: r_{i+1/2}, r_{i-1/2}, their difference, squares, and the dual
+    // cell's area and volume factors
+    double rh, rhm, drh, rh2, y_rh2, dr2h, y_dr2h, rh2m, dr3h, y_dr3h;
+    double lamn, lamh;   // absorber factors at r_i and r_{i+1/2}
+};
+
+typedef const __attribute__((address_space(4))) FusedRow *RowPtr;
+
 struct FusedArgs {
+    using R = double;
     Geo<R> g;
+    const FusedRow *row;       // [nr+1]
     R h;                       // half time step
     int rows;                  // owned rows per workgroup
     int absorb0;               // first row whose absorber factor is below 1
@@ -87,8 +112,9 @@ __device__ __forceinline__ void ff_node_f(const float e[3], const float b[3], fl
     }
 }
 
-template <typename R, bool FF>
-__global__ void __launch_bounds__(kFzT) k_field_fused(const FusedArgs<R> A) {
+template <bool FF>
+__global__ void __launch_bounds__(kFzT) k_field_fused(const FusedArgs A) {
+    using R = double;
     const Geo<R> &g = A.g;
     const int nr = g.nr, nth = g.nth, ld = g.ld;
     const int t = threadIdx.x;
@@ -103,10 +129,16 @@ __global__ void __launch_bounds__(kFzT) k_field_fused(const FusedArgs<R> A) {
     const R fourpi = (R)(4.0 * kPi);
     // column geometry (indices clamped; used only where the stage's
     // condition on j holds)
+    // the row blocks are read through the constant address space: scalar
+    // loads, which wait neither for the next row nor for the stores
+    const RowPtr row = (RowPtr)A.row;
     const bool jlt = j < nth, jgt = j > 0, jin = j > 0 && j < nth;
     const R sn_j = g.sn[jc], sn_j1 = g.sn[min(jc + 1, nth)];
     const R sh_j = g.sh[min(jc, nth - 1)], sh_jm = g.sh[max(jc - 1, 0)];
     const R dcn_j = g.dcn[min(jc, nth - 1)], dcd_j = g.dcd[jc], dthd_j = g.dthd[jc];
+    // reciprocals of the factors that the stages divide by
+    const R y_sn = rcp64(sn_j), y_sh = rcp64(sh_j), y_dcn = rcp64(dcn_j), y_dcd = rcp64(dcd_j),
+            y_dthd = rcp64(dthd_j), y_dth = rcp64(dth), y_dt = rcp64(dt);
 
     // LDS rings (theta neighbours); a ring slot holds one row of one quantity
     __shared__ R lE[2][3][kFzT];          // E^n: r, phi, theta
@@ -130,48 +162,69 @@ __global__ void __launch_bounds__(kFzT) k_field_fused(const FusedArgs<R> A) {
     R d12 = 0, d22 = 0;
     R Ef3[3] = {}, Ef4[3] = {};                     // final E (state) rows q-3, q-4
 
-    for (int q = qs; q <= iL + 4; q++) {
-        // ---- load row q
-        if (q <= nr) {
-            const bool ok = colok;
-            const size_t k = ix(ld, q, jc);
+    // row q is loaded one iteration ahead.  Columns outside the grid load the
+    // nearest one: no stage of an owned column uses their values.
+    R nE[3], nB[3], nJ[3], nf = 0;
+    auto load = [&](int row) {
+        const size_t k0 = ix(ld, row, 0);
+        const unsigned jk = jc;
 #pragma unroll
-            for (int c = 0; c < 3; c++) {
-                sE0[c] = ok ? A.sE[c][k] : (R)0;
-                sB0[c] = ok ? A.sB[c][k] : (R)0;
-                J0[c] = ok ? A.J[c][k] : (R)0;
-            }
-            if constexpr (FF) f0 = ok ? A.f[k] : (R)0;
-            lE[q & 1][0][t] = sE0[0];
-            lE[q & 1][1][t] = sE0[2];
-            lE[q & 1][2][t] = sE0[1];
-            if constexpr (FF) lF[q % 3][t] = f0;
+        for (int c = 0; c < 3; c++) {
+            nE[c] = (A.sE[c] + k0)[jk];
+            nB[c] = (A.sB[c] + k0)[jk];
+            nJ[c] = (A.J[c] + k0)[jk];
         }
+        if constexpr (FF) nf = (A.f + k0)[jk];
+    };
+    load(qs);
+    for (int q = qs; q <= iL + 4; q++) {
+        // ---- row q; past the last row (which only drains the stages) the
+        // last row again, so that the loads are the same in every iteration
+        // and nothing but the next one waits for them
+#pragma unroll
+        for (int c = 0; c < 3; c++) {
+            sE0[c] = nE[c];
+            sB0[c] = nB[c];
+            J0[c] = nJ[c];
+        }
+        f0 = nf;
+        const int fr = q - 4;   // the row stored by this iteration
+        const bool damp = fr >= A.absorb0 && fr >= i0 && fr <= iL;
+        R b0[3];
+        if (damp) {
+#pragma unroll
+            for (int c = 0; c < 3; c++) b0[c] = (A.B0[c] + ix(ld, fr, 0))[(unsigned)jc];
+        }
+        load(min(q + 1, nr));
+        lE[q & 1][0][t] = sE0[0];
+        lE[q & 1][1][t] = sE0[2];
+        lE[q & 1][2][t] = sE0[1];
+        if constexpr (FF) lF[q % 3][t] = f0;
 
         // ---- Faraday half step, row a = q - 1: B^{n+1/2}
         const int a = q - 1;
         if (a >= qs && a <= nr) {
+            const auto &Ra = row[a];
             const R *nb = lE[a & 1][0];   // row a, E state r at j+1 is nb[tr]
             const R epn = lE[a & 1][1][tr];
             const R ern = nb[tr];
             R v[3];
             // B_r (j < nth)
             {
-                R circ = g.rn[a] * (sn_j1 * epn - sn_j * sE1[2]);
-                v[0] = sB1[0] - h * circ / (g.rn2[a] * dcn_j);
+                R circ = Ra.rn * (sn_j1 * epn - sn_j * sE1[2]);
+                v[0] = sB1[0] - quot(h * circ, Ra.rn2 * dcn_j, Ra.y_rn2 * y_dcn);
                 if (!jlt) v[0] = sB1[0];
             }
             if (a < nr) {
                 if (jin) {
-                    R circ = sn_j * (g.rn[a + 1] * sE0[2] - g.rn[a] * sE1[2]);
-                    v[1] = sB1[1] + h * circ / (sn_j * g.dr2n[a]);
+                    R circ = sn_j * (Ra.rn1 * sE0[2] - Ra.rn * sE1[2]);
+                    v[1] = sB1[1] + quot(h * circ, sn_j * Ra.dr2n, y_sn * Ra.y_dr2n);
                 } else {
                     v[1] = (R)0;
                 }
                 if (jlt) {
-                    R circ = dth * (g.rn[a + 1] * sE0[1] - g.rn[a] * sE1[1]) -
-                             g.drn[a] * (ern - sE1[0]);
-                    v[2] = sB1[2] - h * circ / (dth * g.dr2n[a]);
+                    R circ = dth * (Ra.rn1 * sE0[1] - Ra.rn * sE1[1]) - Ra.drn * (ern - sE1[0]);
+                    v[2] = sB1[2] - quot(h * circ, dth * Ra.dr2n, y_dth * Ra.y_dr2n);
                 } else {
                     v[2] = sB1[2];
                 }
@@ -184,7 +237,7 @@ __global__ void __launch_bounds__(kFzT) k_field_fused(const FusedArgs<R> A) {
             lB[a & 3][0][t] = v[0];
             lB[a & 3][1][t] = v[2];
         }
-        __syncthreads();
+        lds_barrier();
 
         // ---- node J_FFE, row b = q - 1 (needs B^{n+1/2} rows b-1, b)
         const int b = q - 1;
@@ -200,11 +253,12 @@ __global__ void __launch_bounds__(kFzT) k_field_fused(const FusedArgs<R> A) {
                     const R er_m = one ? sE1[0] : sE2[0];
                     const R et_i = one ? sE0[1] : sE1[1];
                     const R et_l = lE[ii & 1][2][tl];
-                    R flux = g.rh2[ii] * dcd_j * er_i - g.rh2[ii - 1] * dcd_j * er_m;
-                    if (jlt) flux += sh_j * g.dr2h[ii] * et_i;
-                    if (jgt) flux -= sh_jm * g.dr2h[ii] * et_l;
-                    R dv = flux / (g.dr3h[ii] * dcd_j);
-                    rho = dv / fourpi;
+                    const auto &Ri = row[ii];
+                    R flux = Ri.rh2 * dcd_j * er_i - Ri.rh2m * dcd_j * er_m;
+                    if (jlt) flux += sh_j * Ri.dr2h * et_i;
+                    if (jgt) flux -= sh_jm * Ri.dr2h * et_l;
+                    R dv = quot(flux, Ri.dr3h * dcd_j, Ri.y_dr3h * y_dcd);
+                    rho = quot(dv, fourpi, 1.0 / fourpi);
                 }
                 // node E^n (totals) and B^{n+1/2} (totals)
                 R e[3], bb[3];
@@ -238,9 +292,15 @@ __global__ void __launch_bounds__(kFzT) k_field_fused(const FusedArgs<R> A) {
                 R x2 = e[0] * bb[1] - e[1] * bb[0];
                 {
                     bool ok = b2 > (R)0;
-                    n01 = ok ? rho * x0 / b2 : (R)0;
-                    n11 = ok ? rho * x1 / b2 : (R)0;
-                    n21 = ok ? rho * x2 / b2 : (R)0;
+                    const R y = rcp64(b2);
+                    n01 = quot(rho * x0, b2, y);
+                    n11 = quot(rho * x1, b2, y);
+                    n21 = quot(rho * x2, b2, y);
+                    if (!quot_ok(b2)) {
+                        n01 = ok ? rho * x0 / b2 : (R)0;
+                        n11 = ok ? rho * x1 / b2 : (R)0;
+                        n21 = ok ? rho * x2 / b2 : (R)0;
+                    }
                 }
                 lN[b & 1][t] = n11;
             }
@@ -249,61 +309,57 @@ __global__ void __launch_bounds__(kFzT) k_field_fused(const FusedArgs<R> A) {
         // ---- Ampere, row c = q - 2: E after Ampere
         const int c = q - 2;
         if (c >= qs && c <= nr && (c == 0 || c - 1 >= qs)) {
+            const auto &Rc = row[c];
             R v[3] = {sE2[0], sE2[1], sE2[2]};
             const R *bl = lB[c & 3][0];   // row c, B^{n+1/2} state r, j-1 at [tl]
             const R bp_l = lB[c & 3][1][tl];
             const R jrk = J2[0], jtk = J2[1], jpk = J2[2];
             if (c < nr) {
-                R Ar = g.rh2[c] * dcd_j;
-                R circ = (jlt ? g.rh[c] * sh_j * Bh2[2] : (R)0) -
-                         (jgt ? g.rh[c] * sh_jm * bp_l : (R)0);
+                const R Ar = Rc.rh2 * dcd_j, y = Rc.y_rh2 * y_dcd;
+                R circ = (jlt ? Rc.rh * sh_j * Bh2[2] : (R)0) -
+                         (jgt ? Rc.rh * sh_jm * bp_l : (R)0);
                 R J;
                 if constexpr (FF) {
                     R fs = (R)0.5 * (f2 + f1);
-                    {
-                        J = ((R)1 - fs) * jrk / (dt * Ar) + fs * (R)0.5 * (n02 + n01);
-                    }
+                    J = quot(((R)1 - fs) * jrk, dt * Ar, y_dt * y) + fs * (R)0.5 * (n02 + n01);
                 } else {
-                    J = jrk / (dt * Ar);
+                    J = quot(jrk, dt * Ar, y_dt * y);
                 }
-                v[0] = sE2[0] + (dt * circ / Ar - fourpi * dt * J);
+                v[0] = sE2[0] + (quot(dt * circ, Ar, y) - fourpi * dt * J);
             }
             if (c >= 1 && c < nr) {
                 if (jlt) {
-                    R At = sh_j * g.dr2h[c];
-                    R circ = -(g.rh[c] * sh_j * Bh2[2] - g.rh[c - 1] * sh_j * Bh3[2]);
+                    const R At = sh_j * Rc.dr2h, y = y_sh * Rc.y_dr2h;
+                    R circ = -(Rc.rh * sh_j * Bh2[2] - Rc.rhm * sh_j * Bh3[2]);
                     R J;
                     if constexpr (FF) {
                         R fs = (R)0.5 * (f2 + lF[c % 3][tr]);
-                        {
-                            J = ((R)1 - fs) * jtk / (dt * At) + fs * (R)0.5 * (n12 + lN[c & 1][tr]);
-                        }
+                        J = quot(((R)1 - fs) * jtk, dt * At, y_dt * y) +
+                            fs * (R)0.5 * (n12 + lN[c & 1][tr]);
                     } else {
-                        J = jtk / (dt * At);
+                        J = quot(jtk, dt * At, y_dt * y);
                     }
-                    v[1] = sE2[1] + (dt * circ / At - fourpi * dt * J);
+                    v[1] = sE2[1] + (quot(dt * circ, At, y) - fourpi * dt * J);
                 }
                 if (jin) {
-                    R Ap = dthd_j * g.dr2h[c];
-                    R circ = dth * (g.rh[c] * Bh2[1] - g.rh[c - 1] * Bh3[1]) -
-                             g.drh[c] * (Bh2[0] - bl[tl]);
+                    const R Ap = dthd_j * Rc.dr2h, Vp = Rc.dr3h * dcd_j, yV = Rc.y_dr3h * y_dcd;
+                    R circ = dth * (Rc.rh * Bh2[1] - Rc.rhm * Bh3[1]) -
+                             Rc.drh * (Bh2[0] - bl[tl]);
                     R J;
                     if constexpr (FF) {
                         R fs = f2;
-                        {
-                            J = ((R)1 - fs) * jpk / (g.dr3h[c] * dcd_j) + fs * n22;
-                        }
+                        J = quot(((R)1 - fs) * jpk, Vp, yV) + fs * n22;
                     } else {
-                        J = jpk / (g.dr3h[c] * dcd_j);
+                        J = quot(jpk, Vp, yV);
                     }
-                    v[2] = sE2[2] + (dt * circ / Ap - fourpi * dt * J);
+                    v[2] = sE2[2] + (quot(dt * circ, Ap, y_dthd * Rc.y_dr2h) - fourpi * dt * J);
                 }
             }
 #pragma unroll
             for (int k = 0; k < 3; k++) Ea2[k] = v[k];
             if constexpr (FF) lEa[c & 1][t] = v[1];
         }
-        __syncthreads();
+        lds_barrier();
 
         // ---- force-free correction at nodes, row d = q - 2
         const int d = q - 2;
@@ -330,7 +386,7 @@ __global__ void __launch_bounds__(kFzT) k_field_fused(const FusedArgs<R> A) {
                     } else {
                         bb[2] = (R)0.25 * (lB[(d - 1) & 3][1][tl] + Bh3[2] + bp_l + Bh2[2]);
                     }
-                    ff_node<R>(e, bb, s);
+                    ff_node(e, bb, s);
 #pragma unroll
                     for (int k = 0; k < 3; k++) o[k] = f2 * (s[k] - e[k]);
                 }
@@ -359,27 +415,26 @@ __global__ void __launch_bounds__(kFzT) k_field_fused(const FusedArgs<R> A) {
         }
 
         // ---- Faraday half step, row f = q - 4: B^{n+1}, absorber, stores
-        const int fr = q - 4;
         if (fr >= i0 && fr <= iL) {
             const R epn = lEf[fr & 1][1][tr];
             const R ern = lEf[fr & 1][0][tr];
+            const auto &Rf = row[fr];
             R vb[3];
             {
-                R circ = g.rn[fr] * (sn_j1 * epn - sn_j * Ef4[2]);
-                vb[0] = Bh4[0] - h * circ / (g.rn2[fr] * dcn_j);
+                R circ = Rf.rn * (sn_j1 * epn - sn_j * Ef4[2]);
+                vb[0] = Bh4[0] - quot(h * circ, Rf.rn2 * dcn_j, Rf.y_rn2 * y_dcn);
                 if (!jlt) vb[0] = Bh4[0];
             }
             if (fr < nr) {
                 if (jin) {
-                    R circ = sn_j * (g.rn[fr + 1] * Ef3[2] - g.rn[fr] * Ef4[2]);
-                    vb[1] = Bh4[1] + h * circ / (sn_j * g.dr2n[fr]);
+                    R circ = sn_j * (Rf.rn1 * Ef3[2] - Rf.rn * Ef4[2]);
+                    vb[1] = Bh4[1] + quot(h * circ, sn_j * Rf.dr2n, y_sn * Rf.y_dr2n);
                 } else {
                     vb[1] = (R)0;
                 }
                 if (jlt) {
-                    R circ = dth * (g.rn[fr + 1] * Ef3[1] - g.rn[fr] * Ef4[1]) -
-                             g.drn[fr] * (ern - Ef4[0]);
-                    vb[2] = Bh4[2] - h * circ / (dth * g.dr2n[fr]);
+                    R circ = dth * (Rf.rn1 * Ef3[1] - Rf.rn * Ef4[1]) - Rf.drn * (ern - Ef4[0]);
+                    vb[2] = Bh4[2] - quot(h * circ, dth * Rf.dr2n, y_dth * Rf.y_dr2n);
                 } else {
                     vb[2] = Bh4[2];
                 }
@@ -389,39 +444,39 @@ __global__ void __launch_bounds__(kFzT) k_field_fused(const FusedArgs<R> A) {
             }
             R ve[3] = {Ef4[0], Ef4[1], Ef4[2]};
             // absorbing layer: E damped, B relaxed to its initial value
-            if (fr >= A.absorb0) {
-                const R ln = g.lamn[fr];
-                const R lh = fr < nr ? g.lamh[fr] : (R)1;
+            if (damp) {
+                const R ln = Rf.lamn;
+                const R lh = fr < nr ? Rf.lamh : (R)1;
                 if (!(ln == (R)1 && lh == (R)1)) {
-                    const size_t k = ix(ld, fr, jc);
                     if (fr < nr) {
                         ve[0] *= lh;
-                        const R b0t = A.B0[1][k];
+                        const R b0t = b0[1];
                         vb[1] = b0t + lh * (vb[1] - b0t);
                         if (jlt) {
-                            const R b0p = A.B0[2][k];
+                            const R b0p = b0[2];
                             vb[2] = b0p + lh * (vb[2] - b0p);
                         }
                     }
                     ve[2] *= ln;
                     if (jlt) {
                         ve[1] *= ln;
-                        const R b0r = A.B0[0][k];
+                        const R b0r = b0[0];
                         vb[0] = b0r + ln * (vb[0] - b0r);
                     }
                 }
             }
             if (t >= kFzL && t < kFzL + kFzW && colok) {
-                const size_t k = ix(ld, fr, j);
+                const size_t k0 = ix(ld, fr, 0);
+                const unsigned jk = jc;
 #pragma unroll
                 for (int kk = 0; kk < 3; kk++) {
-                    A.oE[kk][k] = ve[kk];
-                    A.oB[kk][k] = vb[kk];
-                    A.Jz[kk][k] = (R)0;
+                    (A.oE[kk] + k0)[jk] = ve[kk];
+                    (A.oB[kk] + k0)[jk] = vb[kk];
+                    (A.Jz[kk] + k0)[jk] = (R)0;
                 }
             }
         }
-        __syncthreads();
+        lds_barrier();
 
         // ---- shift the own-column histories by one row
         Eat3r = Ea2[0];   // E_r after Ampere, row q-2
@@ -443,12 +498,13 @@ __global__ void __launch_bounds__(kFzT) k_field_fused(const FusedArgs<R> A) {
 }
 
 // Slab height: enough slabs that the grid fills the GPU once.  The rows of a
-// slab are a serial chain (1.6 us a row in FP32, 3.9 in FP64 with the
+// slab are a serial chain (1.6 us a row in FP32, 2.8 in FP64 with the
 // force-free stages), so a grid that cannot fill the GPU takes slabs as low as
 // one row: the six halo rows of each then cost idle CUs, not time.  Step
 // without particles, slabs of at least 32 rows against these: 128^2 FP64 151
-// -> 34 us, 300 x 517 FP32 90 -> 39, 1024^2 FP32 120 -> 78, FP64 215 -> 138;
-// from 2048^2 on 32 rows or more fill the GPU.  `shared`: the height for a
+// -> 34 us, 300 x 517 FP32 90 -> 39, 1024^2 FP32 120 -> 78, FP64 215 -> 138
+// (FP64 before its rows were loaded ahead); from 2048^2 on 32 rows or more
+// fill the GPU.  `shared`: the height for a
 // launch that many systems share (0 = this system alone).
 inline int fused_rows(const ffpic_ctx *c, int shared = 0) {
     if (c->fused_rows > 0) return c->fused_rows;
@@ -459,10 +515,46 @@ inline int fused_rows(const ffpic_ctx *c, int shared = 0) {
     return (c->nr + 1 + slabs - 1) / slabs;
 }
 
+// the row blocks of the FP64 field step, as doubles
+static std::vector<double> fused64_rows(const ffpic_ctx *c) {
+    std::vector<FusedRow> row((size_t)c->nr + 1, FusedRow{});
+    const std::vector<double> *T = c->tab;
+    for (int i = 0; i <= c->nr; i++) {
+        FusedRow &x = row[i];
+        const bool half = i < c->nr;   // r_{i+1/2} is a row of the grid
+        x.rn = T[T_RN][i];
+        x.rn2 = T[T_RN2][i];
+        x.lamn = T[T_LAMN][i];
+        x.y_rn2 = 1.0 / x.rn2;
+        if (half) {
+            x.rn1 = T[T_RN][i + 1];
+            x.drn = T[T_DRN][i];
+            x.dr2n = T[T_DR2N][i];
+            x.y_dr2n = 1.0 / x.dr2n;
+            x.rh = T[T_RH][i];
+            x.lamh = T[T_LAMH][i];
+            x.rh2 = T[T_RH2][i];
+            x.y_rh2 = 1.0 / x.rh2;
+        }
+        if (i >= 1) {
+            x.rhm = T[T_RH][i - 1];
+            x.rh2m = T[T_RH2][i - 1];
+            x.drh = T[T_DRH][i];
+        }
+        x.dr2h = T[T_DR2H][i];
+        x.y_dr2h = 1.0 / x.dr2h;
+        x.dr3h = T[T_DR3H][i];
+        x.y_dr3h = 1.0 / x.dr3h;
+    }
+    const double *p = (const double *)row.data();
+    return {p, p + row.size() * (sizeof(FusedRow) / sizeof(double))};
+}
+
 // FP64 field step (E and B evolved directly)
 static void run_field_fused64(ffpic_ctx *c) {
     using R = double;
-    FusedArgs<R> A{};
+    FusedArgs A{};
+    A.row = (const FusedRow *)c->fz_row64;
     A.g = geo<R>(c);
     A.h = (R)(0.5 * c->dt);
     A.absorb0 = c->absorb_row0;
@@ -474,7 +566,7 @@ static void run_field_fused64(ffpic_ctx *c) {
         A.Jz[k] = (R *)c->Jalt[k];
     }
     A.f = (const R *)c->f;
-    auto kern = c->d.ff_enable ? k_field_fused<R, true> : k_field_fused<R, false>;
+    auto kern = c->d.ff_enable ? k_field_fused<true> : k_field_fused<false>;
     if (c->fused_slots == 0) {   // workgroups resident at once, for the slab height
         int per_cu = 0, cus = 0, dev = 0;
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)kern, kFzT, 0) !=

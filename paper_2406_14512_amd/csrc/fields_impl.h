@@ -7,6 +7,7 @@
 #pragma once
 
 #include "device_common.h"
+#include "math64.h"
 
 namespace ffpic {
 
@@ -218,18 +219,22 @@ __global__ void __launch_bounds__(256) k_mask_group(const MaskJob<R> *__restrict
 
 // force-free correction at a node: E.B projection then the |E| <= |B| cap
 // (Sect. 3); B = 0 gives E = 0
-template <typename R>
-__device__ __forceinline__ void ff_node(const R e[3], const R b[3], R o[3]) {
-    R b2 = b[0] * b[0] + b[1] * b[1] + b[2] * b[2];
-    if (!(b2 > (R)0)) {
-        o[0] = o[1] = o[2] = (R)0;
+__device__ __forceinline__ void ff_node(const double e[3], const double b[3], double o[3]) {
+    const double b2 = b[0] * b[0] + b[1] * b[1] + b[2] * b[2];
+    if (!(b2 > 0.0)) {
+        o[0] = o[1] = o[2] = 0.0;
         return;
     }
-    R eb = e[0] * b[0] + e[1] * b[1] + e[2] * b[2];
-    for (int c = 0; c < 3; c++) o[c] = e[c] - eb * b[c] / b2;
-    R e2 = o[0] * o[0] + o[1] * o[1] + o[2] * o[2];
-    if (e2 >= b2 && e2 > (R)0) {
-        R s = sqrt(b2 / e2);
+    const double eb = e[0] * b[0] + e[1] * b[1] + e[2] * b[2];
+    if (quot_ok(b2)) {
+        const double y = rcp64(b2);
+        for (int c = 0; c < 3; c++) o[c] = e[c] - quot(eb * b[c], b2, y);
+    } else {
+        for (int c = 0; c < 3; c++) o[c] = e[c] - eb * b[c] / b2;
+    }
+    const double e2 = o[0] * o[0] + o[1] * o[1] + o[2] * o[2];
+    if (e2 >= b2 && e2 > 0.0) {
+        const double s = sqrt(b2 / e2);
         for (int c = 0; c < 3; c++) o[c] = s * o[c];
     }
 }

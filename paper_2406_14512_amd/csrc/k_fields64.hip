@@ -4,6 +4,7 @@
 #include "fields_fused.h"
 
 namespace ffpic {
+std::vector<double> fused64_table(const ffpic_ctx *c) { return fused64_rows(c); }
 void field_step64(ffpic_ctx *c) { run_field_fused64(c); }
 void psi_mask64(ffpic_ctx *c) { run_psi_mask<double>(c); }
 }  // namespace ffpic

@@ -27,6 +27,7 @@
 #include <type_traits>
 
 #include "gather.h"
+#include "math64.h"
 
 namespace ffpic {
 
@@ -83,24 +84,10 @@ __device__ __forceinline__ P opaque(P t) {
 }
 
 // ---------------------------------------------------------------------------
-// Quotients and square roots, rounded as the IEEE operations.  Reciprocals
-// and reciprocal roots start from the hardware estimate (about 24 bits) and
-// take Newton steps; a quotient is then a y corrected once by its exact
-// residual, which rounds it correctly but for ties within about 2^-50, so
-// several quotients by one divisor share one reciprocal.  A compiled FP64
-// division is about eleven instructions, one of these three after the
-// reciprocal's five, and a root with its reciprocal 13 instead of 15 and 11.
+// Square roots, rounded as the IEEE operation (quotients: math64.h): the
+// hardware estimate (about 24 bits), Newton steps and the exact residual; a
+// root with its reciprocal is 13 instructions, compiled ones 15 and 11.
 
-__device__ __forceinline__ double rcp64(double b) {
-    double y = __builtin_amdgcn_rcp(b);
-    y = __builtin_fma(__builtin_fma(-b, y, 1.0), y, y);
-    return __builtin_fma(__builtin_fma(-b, y, 1.0), y, y);
-}
-// a / b with y the reciprocal of b
-__device__ __forceinline__ double quot(double a, double b, double y) {
-    const double q = a * y;
-    return __builtin_fma(__builtin_fma(-b, q, a), y, q);
-}
 // sqrt(x) and its reciprocal, x a positive normal number
 __device__ __forceinline__ double root64(double x, double &inv) {
     const double y = __builtin_amdgcn_rsq(x);
@@ -790,7 +777,7 @@ void push64(ffpic_ctx *c, int s) {
     double **a = (double **)S.cur;
     A.R = a[0]; A.TH = a[1]; A.UR = a[2]; A.UT = a[3]; A.UP = a[4];
     A.sct = (const double4 *)c->fz_colc;
-    A.lct = (const double2 *)c->fz_rowc;
+    A.lct = (const double2 *)c->fz_log64;
     A.removed = c->removed + 4 * s;
     A.err = c->err;
     // eight particles per thread spread a chunk's box, patches and flush over

@@ -902,10 +902,15 @@ int ffpic_create(const ffpic_desc *d, void *stream, ffpic_ctx **out) {
                 lct[2 * (k + 1)] = (double)l;
                 lct[2 * (k + 1) + 1] = (double)(l - lct[2 * (k + 1)]);
             }
-            c->fz_rowc = dmalloc(lct.size() * sizeof(double));
-            HCHK(hipMemcpy(c->fz_rowc, lct.data(), lct.size() * sizeof(double), hipMemcpyHostToDevice));
+            // one allocation: sines and cosines, the field step's rows, logarithms
+            const std::vector<double> row = fused64_table(c);
+            const size_t at_row = sct.size(), at_log = at_row + row.size();
+            sct.insert(sct.end(), row.begin(), row.end());
+            sct.insert(sct.end(), lct.begin(), lct.end());
             c->fz_colc = dmalloc(sct.size() * sizeof(double));
             HCHK(hipMemcpy(c->fz_colc, sct.data(), sct.size() * sizeof(double), hipMemcpyHostToDevice));
+            c->fz_row64 = (double *)c->fz_colc + at_row;
+            c->fz_log64 = (double *)c->fz_colc + at_log;
         }
         if (!c->fp64) {
             alloc3(c, c->dE, true);
