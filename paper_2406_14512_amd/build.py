@@ -31,6 +31,7 @@ SOURCES = [
     # atomics instead of the compiler's lane-by-lane pre-reduction loop
     ("k_push32.hip", ["-mllvm", "-amdgpu-atomic-optimizer-strategy=None"]),
     ("k_sort.hip", []),
+    ("k_sort_bucket.hip", []),
     # injected positions follow the oracle's FP64 operation order
     ("k_inject.hip", ["-ffp-contract=off"]),
     # the parent test is evaluated twice and must round the same both times

@@ -268,18 +268,22 @@ void grouped_step(ffpic_batch *b, hipStream_t st, Tables &T) {
         t = mask.place(T);
         ffpic::mask_group_launch(st, t.first, t.second, n, std::min(mask.items(), 4096));
     }
-    // each sorting system's own launches on its own stream's branch, so
-    // that the sorts of different systems may overlap
+    // each sorting system's launches on its stream's branch (shared by the
+    // stream's systems where they are small), so that the sorts of different
+    // systems may overlap
     bool sorts = false;
     for (ffpic_ctx *c : sys) sorts = sorts || ffpic::step_sorts(c);
     if (sorts) {
         BCHK(hipEventRecord(b->fork, st));
         for (auto l : b->streams) BCHK(hipStreamWaitEvent(l, b->fork, 0));
-        for (ffpic_ctx *c : sys) {
-            if (!ffpic::step_sorts(c)) continue;
-            // the push of this step places the sorted order
-            for (int s = 0; s < c->d.nspec; s++) ffpic::sort_species(c, s, true);
-        }
+        // the push of this step places the sorted order
+        std::vector<std::vector<ffpic::SortItem>> items(b->streams.size());
+        for (size_t q = 0; q < sys.size(); q++)
+            if (ffpic::step_sorts(sys[q]))
+                for (int s = 0; s < sys[q]->d.nspec; s++)
+                    items[b->lane[q]].push_back({sys[q], s});
+        for (size_t l = 0; l < items.size(); l++)
+            ffpic::sort_species(items[l].data(), (int)items[l].size(), b->streams[l], true);
         for (size_t l = 0; l < b->streams.size(); l++) {
             BCHK(hipEventRecord(b->join[l], b->streams[l]));
             BCHK(hipStreamWaitEvent(st, b->join[l], 0));

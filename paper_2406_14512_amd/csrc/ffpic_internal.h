@@ -160,6 +160,7 @@ struct ffpic_ctx {
     int64_t sort_cbuf_n = 0;
     uint32_t *sort_tot[FFPIC_MAX_SPECIES] = {};  // stayers, movers, slots before the sort
     int32_t *sort_dest[FFPIC_MAX_SPECIES] = {};   // FP32: place of each slot's particle [cap]
+    uint32_t *sort_bucket[FFPIC_MAX_SPECIES] = {};   // scratch of the bucket form
     bool sort_pending[FFPIC_MAX_SPECIES] = {};   // the next push places the sort
     ffpic::SortPlace place[FFPIC_MAX_SPECIES] = {};
     uint32_t *rs_hist = nullptr, *rs_dtot = nullptr;   // radix sort: digit counts per tile
@@ -205,7 +206,13 @@ Geo<R> geo(const ffpic_ctx *c);
 void psi_mask(ffpic_ctx *c);
 // kill + stable sort by cell; with defer (FP32, incremental sorts) the
 // particles are placed in the new order by the species' next push
-void sort_species(ffpic_ctx *c, int s, bool defer = false);
+// of these species, in launches on stream st shared by those small enough (the
+// others: on their context's stream); contexts of one precision
+struct SortItem {
+    ffpic_ctx *c;
+    int s;
+};
+void sort_species(const SortItem *items, int n, hipStream_t st, bool defer = false);
 void kill_species(ffpic_ctx *c, int s);           // kill without sorting
 void push_species(ffpic_ctx *c, int s);
 void field_step(ffpic_ctx *c);

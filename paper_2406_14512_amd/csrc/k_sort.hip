@@ -16,7 +16,8 @@
 //   3. the live count is the position of the first dead key;
 //   4. the state is gathered into the second buffer.
 //
-// Incremental sort (every later sort).  Between two sorts few particles
+// Incremental sort (every later sort; species that do not fill the GPU take
+// the form of k_sort_bucket.hip instead).  Between two sorts few particles
 // change cell, so only those are sorted:
 //   * a slot holds a "stayer" if its particle's key equals the key the slot
 //     had at the last sort, a "mover" otherwise (dead slots and killed
@@ -48,15 +49,12 @@
 // The result is the same stable order as a full sort of the keys.
 #include <algorithm>
 #include <cstring>
+#include <vector>
 
-#include "device_common.h"
-#include "sort_view.h"
+#include "sort_impl.h"
 
 namespace ffpic {
 
-constexpr int kTile = 1 << kTileShift;      // slots per classify tile (8 per thread)
-constexpr int kTileWords = kTile / 64;      // 64-slot words per tile
-constexpr int kGroup = 1 << kGroupShift;    // tiles per group of the tile scan
 constexpr int kRsItems = 16;                // pairs per thread of a radix tile
 constexpr int kRsTile = 256 * kRsItems;     // pairs per radix tile
 constexpr int kMoverBlocks = 8192;          // blocks of the passes over the movers
@@ -67,45 +65,6 @@ constexpr int kRsBlocks = 2048;             // blocks of a radix pass
         hipError_t e_ = (x);                                                            \
         if (e_ != hipSuccess) throw std::runtime_error(hipGetErrorString(e_));          \
     } while (0)
-
-// ---------------------------------------------------------------------------
-// small device helpers
-
-__device__ __forceinline__ uint64_t lanes_below() {
-    return (1ull << (threadIdx.x & 63)) - 1ull;
-}
-
-// exclusive scan of one value per thread over a block of 256 threads; the
-// block total in *total.  Contains barriers: every thread of the block must
-// call it.
-__device__ __forceinline__ uint64_t block_scan256(uint64_t v, uint64_t *total) {
-    __shared__ uint64_t wt[4];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    uint64_t x = v;
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint64_t y = __shfl_up(x, o, 64);
-        if (lane >= o) x += y;
-    }
-    if (lane == 63) wt[w] = x;
-    __syncthreads();
-    uint64_t pre = 0;
-    for (int u = 0; u < w; u++) pre += wt[u];
-    *total = wt[0] + wt[1] + wt[2] + wt[3];
-    __syncthreads();
-    return pre + x - v;
-}
-
-// lanes of the wave whose (valid) digit equals this lane's
-__device__ __forceinline__ uint64_t digit_peers(uint32_t d, bool valid) {
-    uint64_t m = __ballot(valid);
-#pragma unroll
-    for (int b = 0; b < 8; b++) {
-        const bool bit = (d >> b) & 1u;
-        const uint64_t x = __ballot(bit);
-        m &= bit ? x : ~x;
-    }
-    return m;
-}
 
 __global__ void k_set_i32(int32_t *p, int32_t v) { p[0] = v; }
 
@@ -193,12 +152,6 @@ __global__ void __launch_bounds__(256) k_count_live(int nub, const uint32_t *__r
 }
 
 // permutes all state arrays of a species in one pass over the permutation
-template <typename T, int NA>
-struct PtrSet {
-    const T *src[NA];
-    T *dst[NA];
-};
-
 template <typename T, int NA>
 __global__ void k_gather_set(int nub, const int32_t *__restrict__ nalive,
                              const uint32_t *__restrict__ perm, PtrSet<T, NA> P) {
@@ -442,7 +395,7 @@ static Pairs radix_sort(ffpic_ctx *c, Pairs A, Pairs B, const int32_t *n_dev, in
 // geometry of the sort
 
 // first key past every live one (see the header comment)
-static uint32_t dead_key(const ffpic_ctx *c) {
+uint32_t dead_key(const ffpic_ctx *c) {
     double xa = std::log(c->d.r_abs / c->d.rmin) / c->dlog;
     int64_t iabs = (int64_t)std::floor(xa);
     int64_t k = (iabs + 1) * (int64_t)c->nth;
@@ -481,6 +434,7 @@ void sort_alloc(ffpic_ctx *c, int64_t maxcap, void *(*dmalloc)(size_t)) {
         c->sort_tot[s] = (uint32_t *)dmalloc(4 * 4);
         c->sort_mst[s] = (int32_t *)dmalloc(nk1 * 4);
         if (!c->fp64) c->sort_dest[s] = (int32_t *)dmalloc((size_t)cap * 4);
+        bucket_alloc(c, s, dmalloc);
     }
 }
 
@@ -566,166 +520,9 @@ __global__ void k_offsets_dev(const int32_t *__restrict__ nalive, const uint32_t
 // ---------------------------------------------------------------------------
 // incremental re-sort
 
-struct ClassArgs {
-    int nub, nth, nr;
-    uint32_t dead;
-    const int32_t *nslots, *nsorted;
-    const uint8_t *kill;
-    const int32_t *offold;                      // cell offsets of the last sort
-    unsigned long long *removed;
-    // FP32 state: the cell; FP64 state: r, theta and the geometry
-    int32_t *cell;
-    double *R;
-    const double *TH, *rn, *thn;
-    double rmin, dlog, dth;
-    uint32_t *keys;                             // FP64: key of every slot (out)
-    uint64_t *smask, *mmask;
-    uint32_t *wsm;
-    uint2 *tc;                                  // stayers, movers of each tile
-    uint32_t *tot;                              // [2]: the slot count before the sort
-    uint32_t *tkey, *tval;                      // movers of each tile, compacted in it
-};
-
-// The key a slot had at the last sort is the one whose range of that
-// sort's cell offsets holds the slot: a particle keeps its key since then
-// exactly when its slot lies in [OFF[key], OFF[key+1]).  Two reads of the
-// per-key offsets instead of a stored key per slot (sorted particles of a
-// wave mostly share a key, so the reads share cache lines).  lo, hi: the
-// key's OFF[key], OFF[key+1]; nold: the slots the last sort ordered.
-__device__ __forceinline__ bool in_old_range(int q, int nold, int lo, int hi) {
-    return q < nold && lo <= q && q < hi;
-}
-
-// key of every slot, the removal of killed particles, the class bits and
-// counts, and the movers of the tile compacted in slot order
 template <bool FP64>
 __global__ void __launch_bounds__(256) k_classify(ClassArgs A) {
-    constexpr int K = kTile / 256;
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int base = blockIdx.x * kTile;
-    const int ns = A.nslots[0], no = A.nsorted[0];
-    if (blockIdx.x == 0 && tid == 0) A.tot[2] = (uint32_t)ns;   // for a push that places
-    uint32_t key[K];
-    int cl[K];
-    if (!FP64) {
-        // the cells of all K slots, then for every slot its cell's kill flag
-        // and its key's old offset range, loaded whether needed or not (a
-        // slot without a particle reads those of key 0): with no branch
-        // around them, all 3K loads are in flight together instead of one
-        // round trip after another
-        int cell[K];
-#pragma unroll
-        for (int k = 0; k < K; k++) {
-            const int q = base + k * 256 + tid;
-            cell[k] = q < ns ? A.cell[q] : -1;
-        }
-        uint8_t kf[K];
-        int lo[K], hi[K];
-#pragma unroll
-        for (int k = 0; k < K; k++) {
-            const int c = cell[k];
-            const uint32_t kk =
-                c >= 0 ? (uint32_t)(c >> 16) * (uint32_t)A.nth + (uint32_t)(c & 0xffff) : 0u;
-            key[k] = kk;
-            kf[k] = A.kill[kk];
-            lo[k] = A.offold[kk];
-            hi[k] = A.offold[kk + 1];
-        }
-#pragma unroll
-        for (int k = 0; k < K; k++) {
-            const int q = base + k * 256 + tid;
-            const bool live = cell[k] >= 0;
-            const bool killed = live && kf[k] != 0;
-            if (killed) A.cell[q] = -1;
-            if (!live || killed) key[k] = A.dead;
-            cl[k] = key[k] >= A.dead ? 0 : (in_old_range(q, no, lo[k], hi[k]) ? 1 : 2);
-            count_wave(&A.removed[1], killed);
-        }
-    } else {
-        // the positions of all K slots, their cells, then (as in the FP32
-        // branch) the kill flags and old offset ranges, loaded unconditionally
-        double r[K], th[K];
-#pragma unroll
-        for (int k = 0; k < K; k++) {
-            const int q = base + k * 256 + tid;
-            r[k] = q < ns ? A.R[q] : -1.0;
-            th[k] = q < ns ? A.TH[q] : 0.0;
-        }
-        int cix[K];                                 // i * nth + j, -1: no particle
-#pragma unroll
-        for (int k = 0; k < K; k++) {
-            cix[k] = -1;
-            if (r[k] > 0.0) {
-                int i, j;
-                double a, b;
-                locate64(A.nr, A.nth, A.rmin, A.dlog, A.dth, A.rn, A.thn, r[k], th[k], i, j, a, b);
-                cix[k] = i * A.nth + j;
-            }
-        }
-        uint8_t kf[K];
-        int lo[K], hi[K];
-#pragma unroll
-        for (int k = 0; k < K; k++) {
-            const uint32_t kk = cix[k] >= 0 ? (uint32_t)cix[k] : 0u;
-            kf[k] = A.kill[kk];
-            lo[k] = A.offold[kk];
-            hi[k] = A.offold[kk + 1];
-        }
-#pragma unroll
-        for (int k = 0; k < K; k++) {
-            const int q = base + k * 256 + tid;
-            const bool live = cix[k] >= 0;
-            const bool killed = live && kf[k] != 0;
-            if (killed) A.R[q] = -1.0;
-            key[k] = live && !killed ? (uint32_t)cix[k] : A.dead;
-            if (q < A.nub) A.keys[q] = key[k];
-            cl[k] = key[k] >= A.dead ? 0 : (in_old_range(q, no, lo[k], hi[k]) ? 1 : 2);
-            count_wave(&A.removed[1], killed);
-        }
-    }
-    // the tile's words are staged in LDS and written by 16 lanes at once
-    __shared__ uint64_t wmask[2][kTileWords];
-    __shared__ uint32_t wpre[2][kTileWords];
-    uint64_t mm[K];
-#pragma unroll
-    for (int k = 0; k < K; k++) {
-        const uint64_t sm = __ballot(cl[k] == 1);
-        mm[k] = __ballot(cl[k] == 2);
-        if (lane == 0) {
-            wmask[0][k * 4 + w] = sm;
-            wmask[1][k * 4 + w] = mm[k];
-        }
-    }
-    __syncthreads();
-    const int nwu = (A.nub + 63) >> 6;
-    if (tid < kTileWords) {
-        uint32_t ps = 0, pm = 0;
-        for (int u = 0; u < tid; u++) {
-            ps += (uint32_t)__popcll(wmask[0][u]);
-            pm += (uint32_t)__popcll(wmask[1][u]);
-        }
-        wpre[0][tid] = ps;
-        wpre[1][tid] = pm;
-        const int gw = (base >> 6) + tid;
-        if (gw < nwu) {
-            A.smask[gw] = wmask[0][tid];
-            A.mmask[gw] = wmask[1][tid];
-            A.wsm[gw] = ps | (pm << 16);
-        }
-        if (tid == kTileWords - 1)
-            A.tc[blockIdx.x] = make_uint2(ps + (uint32_t)__popcll(wmask[0][tid]),
-                                          pm + (uint32_t)__popcll(wmask[1][tid]));
-    }
-    __syncthreads();
-    const uint64_t below = lanes_below();
-#pragma unroll
-    for (int k = 0; k < K; k++) {
-        if (cl[k] == 2) {
-            const int r = (int)wpre[1][k * 4 + w] + (int)__popcll(mm[k] & below);
-            A.tkey[base + r] = key[k];
-            A.tval[base + r] = (uint32_t)(base + k * 256 + tid);
-        }
-    }
+    classify_tile<FP64, false>(A, (int)blockIdx.x);
 }
 
 // exclusive scan of the tile counts inside each group of kGroup tiles; the
@@ -790,15 +587,6 @@ __global__ void __launch_bounds__(256) k_movers_dense(int ntile, const uint2 *__
         mk[b + i] = tkey[(size_t)t * kTile + i];
         mv[b + i] = tval[(size_t)t * kTile + i];
     }
-}
-
-// first index in [lo, hi) whose value is >= x
-__device__ __forceinline__ int lower_bound_u32(const uint32_t *a, int lo, int hi, uint32_t x) {
-    while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (a[mid] < x) lo = mid + 1; else hi = mid;
-    }
-    return lo;
 }
 
 // movers per key: the first mover of each run of equal (sorted) keys
@@ -1034,19 +822,23 @@ __global__ void __launch_bounds__(256) k_stayer_dest(ClassView V, int nth,
     }
 }
 
-template <typename T, int NA>
-static PtrSet<T, NA> state_ptrs(ffpic::Species &S) {
-    PtrSet<T, NA> P;
-    for (int a = 0; a < NA; a++) {
-        P.src[a] = (const T *)S.cur[a];
-        P.dst[a] = (T *)S.alt[a];
-    }
-    return P;
-}
-
-static int32_t *perm_out(ffpic_ctx *c, int s) {
+int32_t *perm_out(ffpic_ctx *c, int s) {
     c->perm_valid[s] = c->record_perm && c->perm[s];
     return c->perm_valid[s] ? c->perm[s] : nullptr;
+}
+
+// the next push of species s writes its particles in the sorted order
+void place_by_push(ffpic_ctx *c, int s) {
+    ffpic::Species &S = c->sp[s];
+    SortPlace &P = c->place[s];
+    P.dest = c->sort_dest[s];
+    P.cell = (int32_t *)S.alt[0];
+    P.a = (float *)S.alt[1];
+    P.b = (float *)S.alt[2];
+    P.ur = (float *)S.alt[3];
+    P.ut = (float *)S.alt[4];
+    P.up = (float *)S.alt[5];
+    c->sort_pending[s] = true;
 }
 
 // full sort: key pass, radix sort of all (key, slot) pairs, gather; then the
@@ -1171,15 +963,7 @@ static void sort_incremental(ffpic_ctx *c, int s, bool defer) {
                            c->nth, (const int32_t *)S.cur[0], c->sort_mst[s], c->sort_dest[s],
                            perm);
         FFPIC_LAUNCH_CHECK();
-        SortPlace &P = c->place[s];
-        P.dest = c->sort_dest[s];
-        P.cell = (int32_t *)S.alt[0];
-        P.a = (float *)S.alt[1];
-        P.b = (float *)S.alt[2];
-        P.ur = (float *)S.alt[3];
-        P.ut = (float *)S.alt[4];
-        P.up = (float *)S.alt[5];
-        c->sort_pending[s] = true;
+        place_by_push(c, s);
         c->sort_cur[s] = 1 - t;
         return;
     }
@@ -1206,11 +990,17 @@ static void sort_incremental(ffpic_ctx *c, int s, bool defer) {
     c->sort_cur[s] = 1 - t;
 }
 
-void sort_species(ffpic_ctx *c, int s, bool defer) {
-    ffpic::Species &S = c->sp[s];
-    if (S.nub == 0) return;
-    if (c->sort_valid[s] && c->incremental_sort) sort_incremental(c, s, defer && !c->fp64);
-    else sort_full(c, s);
+void sort_species(const SortItem *items, int n, hipStream_t st, bool defer) {
+    std::vector<SortItem> small;
+    for (int k = 0; k < n; k++) {
+        ffpic_ctx *c = items[k].c;
+        const int s = items[k].s;
+        if (c->sp[s].nub == 0) continue;
+        if (bucket_sort_ok(c, s)) small.push_back(items[k]);
+        else if (c->sort_valid[s] && c->incremental_sort) sort_incremental(c, s, defer && !c->fp64);
+        else sort_full(c, s);
+    }
+    if (!small.empty()) sort_bucketed(small.data(), (int)small.size(), st, defer);
 }
 
 }  // namespace ffpic

@@ -409,7 +409,7 @@ void free_all(ffpic_ctx *c) {
     for (int s = 0; s < FFPIC_MAX_SPECIES; s++) {
         F(c->sort_smask[s]); F(c->sort_mmask[s]); F(c->sort_wsm[s]); F(c->sort_tc[s]);
         F(c->sort_ts[s]); F(c->sort_gs[s]); F(c->sort_tot[s]); F(c->sort_mst[s]);
-        F(c->sort_dest[s]);
+        F(c->sort_dest[s]); F(c->sort_bucket[s]);
     }
     F(c->sort_aux); F(c->sort_kcnt); F(c->sort_cbuf);
     F(c->rs_hist); F(c->rs_dtot); F(c->rs_n); F(c->scan_part);
@@ -528,10 +528,12 @@ void one_step(ffpic_ctx *c, uint32_t ph, bool count_step, int tslot) {
     const bool defer = (ph & FFPIC_PHASE_PUSH) && !c->fp64 &&
                        !((ph & FFPIC_PHASE_INJECT) && c->d.inject_kappa > 0.0) &&
                        !((ph & FFPIC_PHASE_EXTRACT) && c->d.gj_extract > 0.0);
+    SortItem items[FFPIC_MAX_SPECIES];
     for (int s = 0; s < c->d.nspec; s++) {
-        if (ph & FFPIC_PHASE_SORT) sort_species(c, s, defer);
-        else if (ph & FFPIC_PHASE_KILL) kill_species(c, s);
+        items[s] = {c, s};
+        if (!(ph & FFPIC_PHASE_SORT) && (ph & FFPIC_PHASE_KILL)) kill_species(c, s);
     }
+    if (ph & FFPIC_PHASE_SORT) sort_species(items, c->d.nspec, c->stream, defer);
     const bool sources = (c->d.inject_kappa > 0.0 || c->d.gj_extract > 0.0 ||
                           c->d.gamma_th > 0.0) && c->d.nspec > 0;
     if (sources) {
@@ -1057,7 +1059,8 @@ int ffpic_load_particles(ffpic_ctx *c, int s, int64_t n, const double *r, const 
         c->sort_valid[s] = false;   // appended particles: full sort
         int32_t ns = (int32_t)S.nub;
         HCHK(hipMemcpyAsync(c->nslots + s, &ns, sizeof(ns), hipMemcpyHostToDevice, c->stream));
-        sort_species(c, s);
+        const SortItem item{c, s};
+        sort_species(&item, 1, c->stream);
         int32_t alive = 0;
         HCHK(hipMemcpyAsync(&alive, c->nslots + s, sizeof(alive), hipMemcpyDeviceToHost, c->stream));
         HCHK(hipStreamSynchronize(c->stream));
