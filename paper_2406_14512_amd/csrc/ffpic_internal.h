@@ -178,6 +178,7 @@ struct ffpic_ctx {
     int32_t *nalive = nullptr;                // device [FFPIC_MAX_SPECIES]
     unsigned long long *removed = nullptr;    // device [FFPIC_MAX_SPECIES][4]
     uint32_t *err = nullptr;                  // device error word
+    uint32_t *pin = nullptr;                  // pinned host words: error word, counts
     double *red = nullptr;                    // reduction scratch (device)
     size_t red_len = 0;
     int64_t step = 0;
