@@ -397,14 +397,14 @@ int ffpic_restore(ffpic_ctx *ctx, const void *buf, size_t len);
 
 /* Tuning of the fused field step: radial rows per workgroup (each
    workgroup owns a strip of theta columns and a slab of that many rows);
-   0 = automatic (enough slabs to fill the GPU once, at least 32 rows).
+   0 = automatic (enough slabs to fill the GPU once).
    Results do not depend on it.  EINVAL for a negative value. */
 int ffpic_set_field_rows(ffpic_ctx *ctx, int32_t rows);
 
-/* Tuning of the FP32 push: particles per thread of a workgroup's chunk
-   (8, 16 or 32; chunks of 256 threads).  Larger chunks share one field and
-   one current patch among more particles; smaller ones make more
-   workgroups for small systems.  Ignored by the FP64 push.  Results do not
+/* Tuning of the FP32 push: particles per thread of a workgroup's chunk, at
+   most (8, 16 or 32; chunks of 256 threads).  Larger chunks share one field
+   and one current patch among more particles; species too small to fill the
+   GPU with them are taken in smaller ones.  Ignored by the FP64 push.  Results do not
    depend on it beyond the order of floating-point atomic additions.
    EINVAL for another value. */
 int ffpic_set_push_chunk(ffpic_ctx *ctx, int32_t ppt);

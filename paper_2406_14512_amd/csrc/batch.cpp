@@ -62,7 +62,7 @@ struct ffpic_batch {
     int graph_mode = 2;
     int grouped_ppt = 0;              // grouped pushes: particles per thread, 0 = each system's
     int *gctr = nullptr;              // work counters of the grouped launches
-    int push_slots[12] = {}, field_slots[8] = {}, psi_slots = 0;
+    int push_slots[ffpic::kPushKeys] = {}, field_slots[8] = {}, psi_slots = 0;
     int64_t grouped_launches = 0;
     double mode_ms[3] = {0, 0, 0};    // batch-step time of each graph mode at the last tuning
     hipStream_t origin = nullptr;
@@ -220,12 +220,12 @@ size_t table_bound(const ffpic_batch *b, int steps) {
     size_t n = b->ctx.size(), sp = 0;
     for (const ffpic_ctx *c : b->ctx) sp += (size_t)c->d.nspec;
     // per step: two tables (jobs, first items) for each of the flux, mask,
-    // up to 12 push and up to 8 field launches, each array starting at a
+    // up to kPushKeys push and up to 8 field launches, each array starting at a
     // 256-byte boundary
     const size_t pad = 256;
     const size_t psi = n * ffpic::psi_job_bytes() + (n + 1) * 4 + 2 * pad;
     const size_t mask = n * ffpic::mask_job_bytes() + (n + 1) * 4 + 2 * pad;
-    const size_t push = sp * ffpic::push_job_bytes() + (sp + 12) * 4 + 24 * pad;
+    const size_t push = sp * ffpic::push_job_bytes() + (sp + ffpic::kPushKeys) * 4 + 2 * ffpic::kPushKeys * pad;
     const size_t field = n * ffpic::field_job_bytes() + (n + 8) * 4 + 16 * pad;
     return (size_t)steps * (psi + mask + push + field) + pad;
 }
@@ -235,7 +235,7 @@ void grouped_setup(ffpic_batch *b) {
     BCHK(hipMalloc((void **)&b->gctr, 2 * sizeof(int)));
     BCHK(hipMemset(b->gctr, 0, 2 * sizeof(int)));
     BCHK(hipDeviceSynchronize());
-    for (int k = 0; k < 12; k++) b->push_slots[k] = ffpic::push_group_slots(k);
+    for (int k = 0; k < ffpic::kPushKeys; k++) b->push_slots[k] = ffpic::push_group_slots(k);
     for (int k = 0; k < 8; k++) b->field_slots[k] = ffpic::field_group_slots(k);
     b->psi_slots = ffpic::psi_group_slots();
 }
@@ -289,17 +289,20 @@ void grouped_step(ffpic_batch *b, hipStream_t st, Tables &T) {
             BCHK(hipStreamWaitEvent(st, b->join[l], 0));
         }
     }
-    Group push[12];
+    Group push[ffpic::kPushKeys];
+    int64_t slots = 0;                 // of all systems: they share the launches
+    for (ffpic_ctx *c : sys)
+        for (int s = 0; s < c->d.nspec; s++) slots += c->sp[s].nub;
     for (ffpic_ctx *c : sys) {
         for (int s = 0; s < c->d.nspec; s++) {
             if (c->sp[s].nub == 0) continue;
-            Group &g = push[ffpic::push_group_key(c, s, b->grouped_ppt)];
-            const int m = ffpic::push_job(c, s, tmp.data(), b->grouped_ppt);
+            Group &g = push[ffpic::push_group_key(c, s)];
+            const int m = ffpic::push_job(c, s, tmp.data(), b->grouped_ppt, slots);
             g.jobs.insert(g.jobs.end(), tmp.begin(), tmp.begin() + ffpic::push_job_bytes());
             g.starts.push_back(g.items() + m);
         }
     }
-    for (int k = 0; k < 12; k++) {
+    for (int k = 0; k < ffpic::kPushKeys; k++) {
         if (push[k].njobs() == 0 || push[k].items() == 0) continue;
         auto t = push[k].place(T);
         ffpic::push_group_launch(st, k, t.first, t.second, push[k].njobs(),

@@ -45,6 +45,10 @@ struct Geo {
     const R *dthd;  // theta_hi - theta_lo               [nth+1]
 };
 
+// Slots past a species' capacity in its FP32 state arrays: the FP32 push
+// loads and stores whole chunks.
+constexpr int kStatePad = 32 * 256;
+
 enum { T_RN, T_RH, T_RN2, T_RH2, T_DRN, T_DRH, T_DR2N, T_DR2H, T_DR3H, T_DR3N,
        T_LAMN, T_LAMH, T_SN, T_CN, T_SH, T_DCN, T_DCD, T_DTHD, T_THN, T_NTAB };
 static_assert(T_RN == FFPIC_TAB_RN && T_DCN == FFPIC_TAB_DCN && T_THN == FFPIC_TAB_THN &&
@@ -286,8 +290,10 @@ void spectra(ffpic_ctx *c, int s, const ffpic_spectra_req *req, double *dev_out)
 size_t push_job_bytes();
 // ppt: particles per thread of the grouped push (8, 16, 32), 0 = the
 // context's own setting
-int push_group_key(const ffpic_ctx *c, int s, int ppt);   // kernel instance, 0..11
-int push_job(ffpic_ctx *c, int s, void *out, int ppt);
+constexpr int kPushKeys = 4;                     // kernel instances of the grouped push
+int push_group_key(const ffpic_ctx *c, int s);
+// slots: of all systems of the launch
+int push_job(ffpic_ctx *c, int s, void *out, int ppt, int64_t slots);
 int push_group_slots(int key);
 void push_group_launch(hipStream_t st, int key, const void *jobs, const int *starts, int njobs,
                        int grid, int *ctr);

@@ -433,7 +433,7 @@ void sort_alloc(ffpic_ctx *c, int64_t maxcap, void *(*dmalloc)(size_t)) {
         c->sort_gs[s] = (uint2 *)dmalloc((size_t)ng * 8);
         c->sort_tot[s] = (uint32_t *)dmalloc(4 * 4);
         c->sort_mst[s] = (int32_t *)dmalloc(nk1 * 4);
-        if (!c->fp64) c->sort_dest[s] = (int32_t *)dmalloc((size_t)cap * 4);
+        if (!c->fp64) c->sort_dest[s] = (int32_t *)dmalloc((size_t)(cap + kStatePad) * 4);
         bucket_alloc(c, s, dmalloc);
     }
 }

@@ -833,8 +833,9 @@ int ffpic_create(const ffpic_desc *d, void *stream, ffpic_ctx **out) {
             S.narr = c->fp64 ? 5 : 6;
             size_t eb = c->fp64 ? 8 : 4;
             for (int a = 0; a < S.narr; a++) {
-                S.cur[a] = dmalloc((size_t)S.cap * eb);
-                S.alt[a] = dmalloc((size_t)S.cap * eb);
+                const size_t n = (size_t)S.cap + (c->fp64 ? 0 : kStatePad);
+                S.cur[a] = dmalloc(n * eb);
+                S.alt[a] = dmalloc(n * eb);
             }
             maxcap = std::max(maxcap, S.cap);
         }
