@@ -917,10 +917,10 @@ int push_key_index(const PushKey &k) { return (k.shell ? 1 : 0) + (k.place ? 2 :
 //   slots       1      2      4      8     16
 //   1.0e5     8.4    9.6   12.6   19.2   35.2
 //   3.0e5    12.3   12.8   15.8   23.8   45.8
-//   6.5e5    18.4   14.3   18.3   27.9   45.1
+//   6.5e5    19.5   15.2   19.4   29.5   47.8
 //   1.3e6    36.1   29.4   26.3   36.2   57.4
 //   4.0e6   109     82.1   73.6   77.3   90.0
-//   1.0e7   192    135    114    109    118
+//   1.0e7   257    180    151    146    157
 //   2.0e7   509    349    283    268    270
 //   5.0e7  1199    812    664    616    593
 int push_ppt(int setting, int64_t slots) {

@@ -34,6 +34,8 @@ namespace ffpic {
 constexpr int kWG64 = 256;
 constexpr int kTile64 = 640;    // LDS current patch entries per component (FP64)
 constexpr int kFld64 = 320;     // LDS field patch nodes (six components each)
+constexpr int kSide64 = 112;     // rows and columns of a patch, at most
+constexpr int kLone64 = 8;       // in-cell moves left in a wave that add by themselves
 constexpr int kQueue64 = 64;    // queued cell-crossing moves per workgroup
 
 struct P64 {
@@ -211,14 +213,32 @@ __device__ __forceinline__ int guess_j(KArgs A, double th) {
     return g > 0.f ? (g < (float)(A->p.nth - 1) ? (int)g : A->p.nth - 1) : 0;
 }
 
-// radial cell of r from the cell i (nodes rlo, rhi in and out) and the
-// offset in it; the comparisons settle the cell as locate64 does
-template <bool SERIES>
-__device__ __forceinline__ double settle_r(KArgs A, Poly64 K, double r, int &i, double &rlo,
-                                           double &rhi) {
-    while (i > 0 && r < rlo) { i--; rhi = rlo; rlo = at32(A->p.rn, i); }
-    while (i < A->p.nr - 1 && r >= rhi) { i++; rlo = rhi; rhi = at32(A->p.rn, i + 1); }
-    const double a = log_cells<SERIES>(A, K, quot(r, rlo, rcp64(rlo)));
+// Radii of the nodes: with the LDS patches, those of the chunk's rows and one
+// cell around them, with their reciprocals, from LDS; others from the table.
+struct Rows64 {
+    const double2 *t;      // r_i and 1 / r_i of rows [i0, i0 + n)
+    int i0, n;
+};
+template <bool LDS>
+__device__ __forceinline__ double2 row64(KArgs A, const Rows64 &R, int i) {
+    if (LDS && (unsigned)(i - R.i0) < (unsigned)R.n) return R.t[i - R.i0];
+    const double x = at32(A->p.rn, i);
+    return make_double2(x, rcp64(x));
+}
+
+// radial cell of r from the cell i (lo: radius and reciprocal of its inner
+// node, rhi: radius of its outer one, in and out) and the offset in it; the
+// comparisons settle the cell as locate64 does
+template <bool LDS, bool SERIES>
+__device__ __forceinline__ double settle_r(KArgs A, Poly64 K, const Rows64 &R, double r, int &i,
+                                           double2 &lo, double &rhi) {
+    while (i > 0 && r < lo.x) { i--; rhi = lo.x; lo = row64<LDS>(A, R, i); }
+    while (i < A->p.nr - 1 && r >= rhi) {
+        i++;
+        lo = row64<LDS>(A, R, i);
+        rhi = row64<LDS>(A, R, i + 1).x;
+    }
+    const double a = log_cells<SERIES>(A, K, quot(r, lo.x, lo.y));
     return fmin(fmax(a, 0.0), 1.0);
 }
 // polar cell of th from the cell j (theta_j = j dth, as the table holds it)
@@ -311,6 +331,24 @@ __device__ __forceinline__ double row_sum8_64(const double keep[4], const double
     return w + dpp64<0x128>(w);
 }
 
+// The eight adds of a move inside its cell, where the zigzag's two segments
+// share the faces: J_r at (i, j) and (i, j+1), J_theta at (i, j) and (i+1, j),
+// J_phi at the four nodes.  hx, hy: half the radial and polar charge flux, q4
+// a quarter of the azimuthal one, X, Y twice the mid-point.
+__device__ __forceinline__ void values8_64(double hx, double hy, double q4, double X, double Y,
+                                           double s[8]) {
+#pragma clang fp contract(fast)
+    s[1] = hx * Y;
+    s[0] = 2.0 * hx - s[1];
+    s[3] = hy * X;
+    s[2] = 2.0 * hy - s[3];
+    const double u = q4 * X, z = 2.0 * q4 - u;
+    s[7] = u * Y;
+    s[5] = 2.0 * u - s[7];
+    s[6] = z * Y;
+    s[4] = 2.0 * z - s[6];
+}
+
 // where currents go: the LDS patch (tile) or the grid arrays
 template <bool LDS>
 struct Acc64 {
@@ -364,6 +402,8 @@ __device__ __forceinline__ void zigzag64(KArgs A, const Acc64<LDS> &gacc, int i,
 struct Patch64 {
     const double *fld;
     int fi0, fj0, TJ;
+    Rows64 rows;
+    const double4 *cols;   // sine and cosine of the columns from fj0 + 1
 };
 
 // bilinear value of component COMP from the patch node at word offset o and
@@ -400,28 +440,43 @@ __device__ __forceinline__ void push_chunk64(KArgs A0, const Patch64 &F,
     const int kdi = (kq == 3 || kq == 5 || kq == 7) ? 1 : 0;
     const int kdj = (kq == 1 || kq == 6 || kq == 7) ? 1 : 0;
     const int kofs = kcomp * kTile64 + (kdi - acc.ti0) * acc.TJ + kdj - acc.tj0;
+    // the state of a slot (a slot past the last reads the last one and is
+    // ignored)
+    double r, th, ur, ut, up;
+    auto load = [&](KArgs A, int q) {
+        const unsigned qs = (unsigned)(min(q, n - 1) - base);
+        r = at32(A->R + base, qs);
+        th = at32(A->TH + base, qs);
+        ur = at32(A->UR + base, qs);
+        ut = at32(A->UT + base, qs);
+        up = at32(A->UP + base, qs);
+    };
+    load(opaque(A0), base + tid);
 #pragma unroll 1
     for (int k = 0; k < PPT; k++) {
         const KArgs A = opaque(A0);
         const Poly64 K = opaque((Poly64)kPoly64);
         const int q = base + k * kWG64 + tid;
-        // the slot's whole state at once (a slot past the last reads the last
-        // one and is ignored)
-        const unsigned qs = (unsigned)(min(q, n - 1) - base), ql = (unsigned)(q - base);
-        const double r = at32(A->R + base, qs), th = at32(A->TH + base, qs);
-        const double ur = at32(A->UR + base, qs), ut = at32(A->UT + base, qs);
-        const double up = at32(A->UP + base, qs);
+        const unsigned ql = (unsigned)(q - base);
         const bool live = q < n && r > 0.0;
         bool simple = false, cross = false;
-        double k0, k1, k2, k3, p0, p1, p2, p3;   // the eight sums split for the row reduction
+        double hx, hy, q4;                       // in-cell move: see values8_64
         int i = 0, j = 0, di = 0, dj = 0;
         double x1, y1, x2, y2, v1;
         if (live) {
             // ---- old cell and offsets
             i = guess_i(A, r);
             j = guess_j(A, th);
-            double rlo = at32(A->p.rn, i), rhi = at32(A->p.rn, i + 1);
-            const double a = settle_r<SERIES>(A, K, r, i, rlo, rhi);
+            double2 lo;
+            double rhi;
+            if constexpr (LDS) {               // the guesses lie in the box
+                lo = F.rows.t[i - F.rows.i0];
+                rhi = F.rows.t[i + 1 - F.rows.i0].x;
+            } else {
+                lo = row64<false>(A, F.rows, i);
+                rhi = at32(A->p.rn, i + 1);
+            }
+            const double a = settle_r<LDS, SERIES>(A, K, F.rows, r, i, lo, rhi);
             const double b = settle_t(A, th, j);
             const bool killed = at32(A->kill, (unsigned)i * (unsigned)A->p.nth + (unsigned)j) != 0;
             // ---- staggered bilinear gather
@@ -450,7 +505,8 @@ __device__ __forceinline__ void push_chunk64(KArgs A0, const Patch64 &F,
             double st, ct, stl, ctl;
             // (a coarse grid's table divides its cells, see ffpic_create)
             const int js = SERIES ? j : max((int)((float)th * A1->p.gids), 0);
-            sincos_node(K, at32(A1->sct, js), th - js * (SERIES ? A1->p.dth : A1->p.dsub), st, ct, stl,
+            const double4 node = LDS && SERIES ? F.cols[j - F.fj0 - 1] : at32(A1->sct, js);
+            sincos_node(K, node, th - js * (SERIES ? A1->p.dth : A1->p.dsub), st, ct, stl,
                         ctl);
             double E[3], B[3], u[3];
             to_cart(Es[0], Es[1], Es[2], st, ct, E);
@@ -514,7 +570,7 @@ __device__ __forceinline__ void push_chunk64(KArgs A0, const Patch64 &F,
                 // ---- new cell: a move ends at most one cell away, so the
                 // search starts from the old cell
                 int i2 = i, j2 = j;
-                const double a2 = settle_r<SERIES>(A3, K, r2, i2, rlo, rhi);
+                const double a2 = settle_r<LDS, SERIES>(A3, K, F.rows, r2, i2, lo, rhi);
                 const double bb2 = settle_t(A3, th2, j2);
                 di = i2 - i;
                 dj = j2 - j;
@@ -535,27 +591,9 @@ __device__ __forceinline__ void push_chunk64(KArgs A0, const Patch64 &F,
                 cross = !simple;
                 const KArgs A4 = opaque(A);
                 const double Q = A4->p.Q;
-                double s0, s1, s2, s3, s4, s5, s6, s7;
-                {
-#pragma clang fp contract(fast)
-                    const double fx1 = Q * (xm - x1), fy1 = Q * (ym - y1);
-                    const double fx2 = Q * (x2 - xm), fy2 = Q * (y2 - ym);
-                    const double wx1 = 0.5 * (x1 + xm), wy1 = 0.5 * (y1 + ym);
-                    const double wx2 = 0.5 * (xm + x2), wy2 = 0.5 * (ym + y2);
-                    s1 = fx1 * wy1 + fx2 * wy2;
-                    s0 = fx1 * (1.0 - wy1) + fx2 * (1.0 - wy2);
-                    s3 = fy1 * wx1 + fy2 * wx2;
-                    s2 = fy1 * (1.0 - wx1) + fy2 * (1.0 - wx2);
-                    const double qv = Q * v1, qx0 = qv * (1.0 - xm), qx1 = qv * xm;
-                    s4 = qx0 * (1.0 - ym);
-                    s5 = qx1 * (1.0 - ym);
-                    s6 = qx0 * ym;
-                    s7 = qx1 * ym;
-                }
-                k0 = b0 ? s4 : s0; p0 = b0 ? s0 : s4;
-                k1 = b0 ? s5 : s1; p1 = b0 ? s1 : s5;
-                k2 = b0 ? s6 : s2; p2 = b0 ? s2 : s6;
-                k3 = b0 ? s7 : s3; p3 = b0 ? s3 : s7;
+                hx = 0.5 * Q * (x2 - x1);
+                hy = 0.5 * Q * (y2 - y1);
+                q4 = 0.25 * Q * v1;
                 if (LDS && cfl) {
                     // outside the patch: straight to the grid
                     const Acc64<false> gacc{nullptr, 0, 0, 0, {A4->J[0], A4->J[1], A4->J[2]},
@@ -565,23 +603,34 @@ __device__ __forceinline__ void push_chunk64(KArgs A0, const Patch64 &F,
                 }
             }
         }
+        // ---- the next particle's state is loaded here, past the part that needs
+        // the registers, and travels during the deposit
         // ---- in-cell moves, one cell per 16-lane row and pass: the lanes of a
         // row whose cell is that of the row's first pending lane sum their eight
         // values over the row, and lanes 0..7 of the row add one sum each.  Every
         // pass retires at least the first pending lane of each row, so the loop
-        // ends within 16 passes with every in-cell move deposited.
+        // ends within 16 passes with every in-cell move deposited; when few
+        // lanes of the wave are left, they add their values by themselves.
+        if (PPT > 1) load(opaque(A0), q + kWG64);
         bool pend = simple;
         const int c = LDS ? i * acc.TJ + j : (i << 16) | j;
+        const double X = x1 + x2, Y = y1 + y2;   // twice the mid-point
+        unsigned long long m = __ballot(pend);
 #pragma unroll 1
-        while (true) {
-            const unsigned long long m = __ballot(pend);
-            if (m == 0ull) break;
+        while (m != 0ull) {
             const unsigned rowm = (unsigned)(m >> (lane & 48)) & 0xffffu;
             const int src = rowm ? (lane & 48) + __builtin_ctz(rowm) : lane;
             const int lc = __shfl(c, src, 64);
             const bool part = pend && c == lc;
-            const double pk[4] = {part ? k0 : 0.0, part ? k1 : 0.0, part ? k2 : 0.0, part ? k3 : 0.0};
-            const double pp[4] = {part ? p0 : 0.0, part ? p1 : 0.0, part ? p2 : 0.0, part ? p3 : 0.0};
+            double s[8];
+            values8_64(part ? hx : 0.0, part ? hy : 0.0, part ? q4 : 0.0, part ? X : 0.0,
+                       part ? Y : 0.0, s);
+            double pk[4], pp[4];
+#pragma unroll
+            for (int u = 0; u < 4; u++) {
+                pk[u] = b0 ? s[4 + u] : s[u];
+                pp[u] = b0 ? s[u] : s[4 + u];
+            }
             const double v = row_sum8_64(pk, pp, b1, b2);
             // a row with pending lanes has participants: its leader
             if ((lane & 8) == 0 && rowm != 0u) {
@@ -592,6 +641,21 @@ __device__ __forceinline__ void push_chunk64(KArgs A0, const Patch64 &F,
                 }
             }
             pend = pend && !part;
+            m = __ballot(pend);
+            if (__popcll(m) <= kLone64) {
+                if (pend) {
+                    values8_64(hx, hy, q4, X, Y, s);
+                    acc.add(0, i, j, s[0]);
+                    acc.add(0, i, j + 1, s[1]);
+                    acc.add(1, i, j, s[2]);
+                    acc.add(1, i + 1, j, s[3]);
+                    acc.add(2, i, j, s[4]);
+                    acc.add(2, i + 1, j, s[5]);
+                    acc.add(2, i, j + 1, s[6]);
+                    acc.add(2, i + 1, j + 1, s[7]);
+                }
+                break;
+            }
         }
         // ---- moves that leave their cell: queued and deposited after the
         // chunk, where one wave takes them all
@@ -625,19 +689,25 @@ __device__ __forceinline__ void push_chunk64(KArgs A0, const Patch64 &F,
 // that of the single-precision cell guesses with a margin of one cell.
 // Four waves per SIMD: 128 VGPRs and a quarter of a CU's LDS each.
 //
-// Bound by VALU issue (0.80 of the SIMDs' slots at the 2.09 GHz that FP64
-// work runs at, 923 instructions a particle).  5e7 particles of the 2048^2
-// sheet: 1.74 ms (2.3 TB/s of its 80 B a particle) against 2.60 ms for one
-// particle per thread with the library's divisions, roots, sine, logarithm
-// and arctangent and the gather from global memory (1751 instructions); the
-// same sums on the FP64 matrix cores (4x4x4 products by ones in place of the
-// DPP rows) measured 1.83 ms, with fewer instructions but a longer chain.
+// Bound by VALU issue (0.87 of the SIMDs' slots at the 2.0 GHz that FP64
+// work runs at, 889 instructions a particle, two thirds of them FP64).  5e7
+// particles of the 2048^2 sheet: 1.59 ms (2.5 TB/s of its 80 B a particle)
+// against 2.60 ms for one particle per thread with the library's divisions,
+// roots, sine, logarithm and arctangent and the gather from global memory
+// (1751 instructions).  Of the last 0.10 ms, 0.06 came from loading the next
+// state past the part that needs the registers, 0.03 from radii, sines and
+// cosines in LDS, 0.01 from the deposit's values masked before they are
+// formed.  The same sums on the FP64 matrix cores (4x4x4 products by ones in
+// place of the DPP rows) took 0.09 ms more, with fewer instructions but a
+// longer chain; three waves per SIMD without spills take the same time.
 template <int PPT, bool SERIES>
 __global__ void __launch_bounds__(kWG64) __attribute__((amdgpu_waves_per_eu(4, 4)))
 k_push64(const Push64Args A) {
     const KArgs KA = (KArgs)__builtin_amdgcn_kernarg_segment_ptr();
     __shared__ double tile[3 * kTile64];
     __shared__ double fld[6 * kFld64];
+    __shared__ double2 rows[kSide64];
+    __shared__ double4 cols[kSide64];
     __shared__ Move64 queue[kQueue64];
     __shared__ int box[4];
     __shared__ int qn;
@@ -688,7 +758,9 @@ k_push64(const Push64Args A) {
     const int TI = i1 - i0 + 4, TJ = j1 - j0 + 4;
     const int fi0 = max(i0 - 1, 0), fj0 = j0 - 1;
     const int TIf = i1 + 1 - fi0 + 1, TJf = j1 - j0 + 3;
-    const bool use_lds = TI * TJ <= kTile64 && TIf * TJf <= kFld64;
+    const bool use_lds = TI * TJ <= kTile64 && TIf * TJf <= kFld64 &&
+                         TI <= kSide64 && TJ <= kSide64;
+    const int r0 = max(i0 - 1, 0), nrow = min(i1 + 2, p.nr) - r0 + 1;
     Counts64 cnt{0, 0, 0};
     if (use_lds) {
         const int m = TI * TJ;
@@ -710,8 +782,14 @@ k_push64(const Push64Args A) {
             fld[e * 6 + 4] = A.B[1][gn];
             fld[e * 6 + 5] = par * A.B[2][gh];
         }
+        for (int e = tid; e < nrow; e += kWG64) {
+            const double x = A.p.rn[r0 + e];
+            rows[e] = make_double2(x, rcp64(x));
+        }
+        if (SERIES)
+            for (int e = tid; e <= j1 - j0; e += kWG64) cols[e] = A.sct[j0 + e];
         __syncthreads();
-        const Patch64 F{fld, fi0, fj0, TJf};
+        const Patch64 F{fld, fi0, fj0, TJf, Rows64{rows, r0, nrow}, cols};
         const Acc64<true> acc{tile, i0 - 1, j0 - 1, TJ, {A.J[0], A.J[1], A.J[2]}, p.ld};
         push_chunk64<true, PPT, SERIES>(KA, F, acc, nullptr, n, base, queue, &qn, cnt);
         __syncthreads();
