@@ -163,7 +163,7 @@ struct ffpic_ctx {
     void *sort_cbuf = nullptr;                // movers' state, compacted [narr * cbuf_n]
     int64_t sort_cbuf_n = 0;
     uint32_t *sort_tot[FFPIC_MAX_SPECIES] = {};  // stayers, movers, slots before the sort
-    int32_t *sort_dest[FFPIC_MAX_SPECIES] = {};   // FP32: place of each slot's particle [cap]
+    int32_t *sort_dest[FFPIC_MAX_SPECIES] = {};   // place of each slot's particle [cap + padding]
     uint32_t *sort_bucket[FFPIC_MAX_SPECIES] = {};   // scratch of the bucket form
     bool sort_pending[FFPIC_MAX_SPECIES] = {};   // the next push places the sort
     ffpic::SortPlace place[FFPIC_MAX_SPECIES] = {};
@@ -209,7 +209,7 @@ Geo<R> geo(const ffpic_ctx *c);
 
 // kernels (launchers); all enqueue on c->stream
 void psi_mask(ffpic_ctx *c);
-// kill + stable sort by cell; with defer (FP32, incremental sorts) the
+// kill + stable sort by cell; with defer (incremental sorts) the
 // particles are placed in the new order by the species' next push
 // of these species, in launches on stream st shared by those small enough (the
 // others: on their context's stream); contexts of one precision
@@ -219,7 +219,10 @@ struct SortItem {
 };
 void sort_species(const SortItem *items, int n, hipStream_t st, bool defer = false);
 void kill_species(ffpic_ctx *c, int s);           // kill without sorting
-void push_species(ffpic_ctx *c, int s);
+void push_all(ffpic_ctx *c);               // every species
+// host bookkeeping after the launch of a species' push: one that placed the sort
+// leaves the new order in the second buffer
+void after_push(ffpic_ctx *c, int s);
 void field_step(ffpic_ctx *c);
 void convert_loaded(ffpic_ctx *c, int s, int64_t off, int64_t n, const double *r,
                     const double *th, const double *ur, const double *uth, const double *uph);

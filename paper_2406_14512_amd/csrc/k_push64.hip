@@ -24,6 +24,7 @@
 // workgroup over the bounding box of its (cell-sorted) particles, in-cell
 // moves summed across each 16-lane row first (DPP, one cell per row and
 // pass), one global FP64 atomic per non-zero patch entry.
+#include <algorithm>
 #include <type_traits>
 
 #include "gather.h"
@@ -62,6 +63,15 @@ struct Push64Args {
     double *J[3];
     unsigned long long *removed;
     uint32_t *err;
+    // a push that places its species' sort: the place of each slot's particle
+    // (-1: none) and the state of the new order
+    const int32_t *dest;
+    double *oR, *oTH, *oUR, *oUT, *oUP;
+};
+
+// the species of one launch (blockIdx.y)
+struct Push64Jobs {
+    Push64Args job[FFPIC_MAX_SPECIES];
 };
 
 // The arguments as the kernel finds them in constant memory.  The particle
@@ -78,6 +88,9 @@ __device__ __forceinline__ T &at32(T *base, unsigned idx) {
         reinterpret_cast<char *>(const_cast<typename std::remove_const<T>::type *>(base)) +
         (size_t)(idx * (unsigned)sizeof(T)));
 }
+
+// element `idx` of an array of any length
+__device__ __forceinline__ double &at64(double *base, int idx) { return base[(size_t)idx]; }
 
 template <typename P>
 __device__ __forceinline__ P opaque(P t) {
@@ -426,7 +439,7 @@ struct Counts64 {
 
 // the particles of one chunk (kWG64 * PPT slots from base), the patches in
 // LDS (LDS) or the grid arrays read and added to directly
-template <bool LDS, int PPT, bool SERIES>
+template <bool LDS, int PPT, bool SERIES, bool PLACE>
 __device__ __forceinline__ void push_chunk64(KArgs A0, const Patch64 &F,
                                              const Acc64<LDS> &acc, double *kg, int n, int base,
                                              Move64 *queue, int *qn, Counts64 &cnt) {
@@ -443,6 +456,7 @@ __device__ __forceinline__ void push_chunk64(KArgs A0, const Patch64 &F,
     // the state of a slot (a slot past the last reads the last one and is
     // ignored)
     double r, th, ur, ut, up;
+    int dn = -1;               // PLACE: the place of its particle
     auto load = [&](KArgs A, int q) {
         const unsigned qs = (unsigned)(min(q, n - 1) - base);
         r = at32(A->R + base, qs);
@@ -450,6 +464,7 @@ __device__ __forceinline__ void push_chunk64(KArgs A0, const Patch64 &F,
         ur = at32(A->UR + base, qs);
         ut = at32(A->UT + base, qs);
         up = at32(A->UP + base, qs);
+        if constexpr (PLACE) dn = at32(A->dest + base, qs);
     };
     load(opaque(A0), base + tid);
 #pragma unroll 1
@@ -458,7 +473,8 @@ __device__ __forceinline__ void push_chunk64(KArgs A0, const Patch64 &F,
         const Poly64 K = opaque((Poly64)kPoly64);
         const int q = base + k * kWG64 + tid;
         const unsigned ql = (unsigned)(q - base);
-        const bool live = q < n && r > 0.0;
+        const int dq = dn;
+        const bool live = q < n && r > 0.0 && (!PLACE || dq >= 0);
         bool simple = false, cross = false;
         double hx, hy, q4;                       // in-cell move: see values8_64
         int i = 0, j = 0, di = 0, dj = 0;
@@ -564,7 +580,8 @@ __device__ __forceinline__ void push_chunk64(KArgs A0, const Patch64 &F,
             cnt.star += star;
             cnt.abs += absb;
             if (!keep) {
-                at32(A3->R + base, ql) = -1.0;
+                if constexpr (PLACE) at64(A3->oR, dq) = -1.0;
+                else at32(A3->R + base, ql) = -1.0;
             } else {
                 const double st2 = quot(w, r2, ir2), ct2 = quot(z, r2, ir2);
                 // ---- new cell: a move ends at most one cell away, so the
@@ -577,11 +594,19 @@ __device__ __forceinline__ void push_chunk64(KArgs A0, const Patch64 &F,
                 const bool cfl = di > 1 || di < -1 || dj > 1 || dj < -1;
                 if (cfl) atomicOr(A3->err, FFPIC_ERR_CFL);
                 x1 = a; y1 = b; x2 = di + a2; y2 = dj + bb2;
-                at32(A3->R + base, ql) = r2;
-                at32(A3->TH + base, ql) = th2;
-                at32(A3->UR + base, ql) = ux * st2 + uz * ct2;
-                at32(A3->UT + base, ql) = ux * ct2 - uz * st2;
-                at32(A3->UP + base, ql) = uy;
+                if constexpr (PLACE) {
+                    at64(A3->oR, dq) = r2;
+                    at64(A3->oTH, dq) = th2;
+                    at64(A3->oUR, dq) = ux * st2 + uz * ct2;
+                    at64(A3->oUT, dq) = ux * ct2 - uz * st2;
+                    at64(A3->oUP, dq) = uy;
+                } else {
+                    at32(A3->R + base, ql) = r2;
+                    at32(A3->TH + base, ql) = th2;
+                    at32(A3->UR + base, ql) = ux * st2 + uz * ct2;
+                    at32(A3->UT + base, ql) = ux * ct2 - uz * st2;
+                    at32(A3->UP + base, ql) = uy;
+                }
                 // zigzag with both ends in the cell: the two segments share
                 // the four faces of the cell, the relay point is the
                 // mid-point (both ends lie in [0, 1]), and so is the cell of
@@ -700,10 +725,11 @@ __device__ __forceinline__ void push_chunk64(KArgs A0, const Patch64 &F,
 // formed.  The same sums on the FP64 matrix cores (4x4x4 products by ones in
 // place of the DPP rows) took 0.09 ms more, with fewer instructions but a
 // longer chain; three waves per SIMD without spills take the same time.
-template <int PPT, bool SERIES>
+template <int PPT, bool SERIES, bool PLACE>
 __global__ void __launch_bounds__(kWG64) __attribute__((amdgpu_waves_per_eu(4, 4)))
-k_push64(const Push64Args A) {
-    const KArgs KA = (KArgs)__builtin_amdgcn_kernarg_segment_ptr();
+k_push64(const Push64Jobs) {
+    const KArgs KA = (KArgs)__builtin_amdgcn_kernarg_segment_ptr() + blockIdx.y;
+    const auto &A = *KA;
     __shared__ double tile[3 * kTile64];
     __shared__ double fld[6 * kFld64];
     __shared__ double2 rows[kSide64];
@@ -711,9 +737,10 @@ k_push64(const Push64Args A) {
     __shared__ Move64 queue[kQueue64];
     __shared__ int box[4];
     __shared__ int qn;
-    const P64 &p = A.p;
+    const auto &p = A.p;
     const int tid = threadIdx.x, lane = tid & 63;
-    const int n = min(A.nub, A.nslots[0]);
+    // PLACE: the slots before the sort (the slot count holds the new order's)
+    const int n = min(A.nub, A.nslots[PLACE ? 2 : 0]);
     const int base = (int)blockIdx.x * (kWG64 * PPT);
     if (base >= n) return;    // no slot in the chunk (uniform)
     double rb[PPT], tb[PPT];
@@ -791,7 +818,7 @@ k_push64(const Push64Args A) {
         __syncthreads();
         const Patch64 F{fld, fi0, fj0, TJf, Rows64{rows, r0, nrow}, cols};
         const Acc64<true> acc{tile, i0 - 1, j0 - 1, TJ, {A.J[0], A.J[1], A.J[2]}, p.ld};
-        push_chunk64<true, PPT, SERIES>(KA, F, acc, nullptr, n, base, queue, &qn, cnt);
+        push_chunk64<true, PPT, SERIES, PLACE>(KA, F, acc, nullptr, n, base, queue, &qn, cnt);
         __syncthreads();
         for (int e = tid; e < m; e += kWG64) {
             const int ti = e / TJ, tj = e - ti * TJ;
@@ -808,7 +835,7 @@ k_push64(const Push64Args A) {
         // component of the row sum this lane adds (see push_chunk64)
         const int kc = (lane & 1) ? 2 : ((lane & 2) ? 1 : 0);
         double *kg = kc == 0 ? A.J[0] : (kc == 1 ? A.J[1] : A.J[2]);
-        push_chunk64<false, PPT, SERIES>(KA, Patch64{}, acc, kg, n, base, queue, &qn, cnt);
+        push_chunk64<false, PPT, SERIES, PLACE>(KA, Patch64{}, acc, kg, n, base, queue, &qn, cnt);
     }
     int tk = cnt.kill, ts = cnt.star, ta = cnt.abs;
     for (int o = 32; o >= 1; o >>= 1) {
@@ -823,9 +850,8 @@ k_push64(const Push64Args A) {
     }
 }
 
-void push64(ffpic_ctx *c, int s) {
+static Push64Args push64_job(ffpic_ctx *c, int s) {
     ffpic::Species &S = c->sp[s];
-    if (S.nub == 0) return;
     Push64Args A{};
     P64 &p = A.p;
     p.nr = c->nr; p.nth = c->nth; p.ld = c->ld;
@@ -845,7 +871,8 @@ void push64(ffpic_ctx *c, int s) {
     p.rr = c->d.rr_coef * rr_factor(c) * fabs(qm) * fabs(qm) * fabs(qm);
     p.shell_r = c->d.shell_r;
     A.nub = (int)S.nub;
-    A.nslots = c->nslots + s;
+    const bool place = c->sort_pending[s];
+    A.nslots = place ? (const int32_t *)c->sort_tot[s] : c->nslots + s;
     A.kill = c->kill;
     for (int k = 0; k < 3; k++) {
         A.E[k] = (const double *)c->E[k];
@@ -854,25 +881,56 @@ void push64(ffpic_ctx *c, int s) {
     }
     double **a = (double **)S.cur;
     A.R = a[0]; A.TH = a[1]; A.UR = a[2]; A.UT = a[3]; A.UP = a[4];
+    if (place) {
+        double **o = (double **)S.alt;
+        A.dest = c->sort_dest[s];
+        A.oR = o[0]; A.oTH = o[1]; A.oUR = o[2]; A.oUT = o[3]; A.oUP = o[4];
+    }
     A.sct = (const double4 *)c->fz_colc;
     A.lct = (const double2 *)c->fz_log64;
     A.removed = c->removed + 4 * s;
     A.err = c->err;
-    // eight particles per thread spread a chunk's box, patches and flush over
-    // 2048 particles (5e7 particles, 2048^2 sheet: 1.74 ms against 1.80 with
-    // four and 1.99 with one); a species too small to fill the GPU (1024
-    // workgroups resident) several times that way takes fewer per thread
-    // (1e5 particles: 11.5 us with one, about 30 with eight)
-    const int64_t per = (S.nub + kWG64 - 1) / kWG64;
+    return A;
+}
+
+using Push64Kern = void (*)(const Push64Jobs);
+
+template <bool PLACE>
+static Push64Kern push64_kern(int ppt, bool series) {
+    return !series ? k_push64<1, false, PLACE>
+                   : (ppt == 1 ? k_push64<1, true, PLACE>
+                               : (ppt == 2 ? k_push64<2, true, PLACE> : k_push64<8, true, PLACE>));
+}
+
+void push64(ffpic_ctx *c) {
     // (coarse grids, past the range of the series, take the library's
     // logarithm and arctangent)
     const bool series = c->dlog <= 0.0625 && c->dth <= 0.0625;
-    const int ppt = !series || per < 8 * 1024 ? 1 : (per < 16 * 1024 ? 2 : 8);
-    auto kern = !series ? k_push64<1, false>
-                        : (ppt == 1 ? k_push64<1, true>
-                                    : (ppt == 2 ? k_push64<2, true> : k_push64<8, true>));
-    hipLaunchKernelGGL(kern, dim3((unsigned)((per + ppt - 1) / ppt)), dim3(kWG64), 0, c->stream, A);
-    FFPIC_LAUNCH_CHECK();
+    for (int place = 0; place < 2; place++) {
+        // the species whose kernel is the same share a launch
+        Push64Jobs P{};
+        int m = 0;
+        int64_t most = 0, per = 0;
+        for (int s = 0; s < c->d.nspec; s++) {
+            const int64_t w = (c->sp[s].nub + kWG64 - 1) / kWG64;
+            if (w == 0 || (int)c->sort_pending[s] != place) continue;
+            P.job[m++] = push64_job(c, s);
+            most = std::max(most, w);
+            per += w;
+        }
+        if (m == 0) continue;
+        // eight particles per thread spread a chunk's box, patches and flush
+        // over 2048 particles (5e7 particles, 2048^2 sheet: 1.74 ms against
+        // 1.80 with four and 1.99 with one); species too small to fill the GPU
+        // (1024 workgroups resident) several times that way take fewer per
+        // thread (1e5 particles: 11.5 us with one, about 30 with eight)
+        const int ppt = !series || per < 8 * 1024 ? 1 : (per < 16 * 1024 ? 2 : 8);
+        const Push64Kern kern = place ? push64_kern<true>(ppt, series) : push64_kern<false>(ppt, series);
+        hipLaunchKernelGGL(kern, dim3((unsigned)((most + ppt - 1) / ppt), m), dim3(kWG64), 0,
+                           c->stream, P);
+        FFPIC_LAUNCH_CHECK();
+    }
+    for (int s = 0; s < c->d.nspec; s++) after_push(c, s);
 }
 
 }  // namespace ffpic

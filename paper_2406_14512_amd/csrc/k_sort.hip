@@ -433,7 +433,7 @@ void sort_alloc(ffpic_ctx *c, int64_t maxcap, void *(*dmalloc)(size_t)) {
         c->sort_gs[s] = (uint2 *)dmalloc((size_t)ng * 8);
         c->sort_tot[s] = (uint32_t *)dmalloc(4 * 4);
         c->sort_mst[s] = (int32_t *)dmalloc(nk1 * 4);
-        if (!c->fp64) c->sort_dest[s] = (int32_t *)dmalloc((size_t)(cap + kStatePad) * 4);
+        c->sort_dest[s] = (int32_t *)dmalloc((size_t)(cap + kStatePad) * 4);
         bucket_alloc(c, s, dmalloc);
     }
 }
@@ -771,6 +771,8 @@ __global__ void __launch_bounds__(256) k_mover_dest(ClassView V, const uint32_t 
 // tile and group counts are read once per wave with scalar loads.
 constexpr int kDestSlots = 8;
 
+// (FP64: the slots' keys instead of cells)
+template <bool FP64>
 __global__ void __launch_bounds__(256) k_stayer_dest(ClassView V, int nth,
                                                      const int32_t *__restrict__ cell,
                                                      const int32_t *__restrict__ mst,
@@ -790,8 +792,9 @@ __global__ void __launch_bounds__(256) k_stayer_dest(ClassView V, int nth,
     int32_t ms[kDestSlots];
 #pragma unroll
     for (int k = 0; k < kDestSlots; k++) {
-        const uint32_t key =
-            c[k] >= 0 ? (uint32_t)(c[k] >> 16) * (uint32_t)nth + (uint32_t)(c[k] & 0xffff) : 0u;
+        uint32_t key = (uint32_t)max(c[k], 0);
+        if (!FP64 && c[k] >= 0)
+            key = (uint32_t)(c[k] >> 16) * (uint32_t)nth + (uint32_t)(c[k] & 0xffff);
         ms[k] = mst[key];
     }
     int32_t d[kDestSlots];
@@ -830,6 +833,8 @@ int32_t *perm_out(ffpic_ctx *c, int s) {
 // the next push of species s writes its particles in the sorted order
 void place_by_push(ffpic_ctx *c, int s) {
     ffpic::Species &S = c->sp[s];
+    c->sort_pending[s] = true;
+    if (c->fp64) return;       // its push takes the buffers themselves
     SortPlace &P = c->place[s];
     P.dest = c->sort_dest[s];
     P.cell = (int32_t *)S.alt[0];
@@ -838,7 +843,6 @@ void place_by_push(ffpic_ctx *c, int s) {
     P.ur = (float *)S.alt[3];
     P.ut = (float *)S.alt[4];
     P.up = (float *)S.alt[5];
-    c->sort_pending[s] = true;
 }
 
 // full sort: key pass, radix sort of all (key, slot) pairs, gather; then the
@@ -955,13 +959,16 @@ static void sort_incremental(ffpic_ctx *c, int s, bool defer) {
     int32_t *perm = perm_out(c, s);
     if (defer) {
         // the next push reads the particles in the old order and writes
-        // them in the new one (FP32): it reads where each goes
+        // them in the new one: it reads where each goes
         hipLaunchKernelGGL(k_mover_dest, dim3(nbm), dim3(256), 0, c->stream, V, M.k, M.v, offold,
                            c->sort_dest[s], perm);
-        hipLaunchKernelGGL(k_stayer_dest, dim3((nub + 256 * kDestSlots - 1) / (256 * kDestSlots)),
-                           dim3(256), 0, c->stream, V,
-                           c->nth, (const int32_t *)S.cur[0], c->sort_mst[s], c->sort_dest[s],
-                           perm);
+        const dim3 grid((nub + 256 * kDestSlots - 1) / (256 * kDestSlots));
+        if (c->fp64)
+            hipLaunchKernelGGL(k_stayer_dest<true>, grid, dim3(256), 0, c->stream, V, c->nth,
+                               (const int32_t *)c->keys[0], c->sort_mst[s], c->sort_dest[s], perm);
+        else
+            hipLaunchKernelGGL(k_stayer_dest<false>, grid, dim3(256), 0, c->stream, V, c->nth,
+                               (const int32_t *)S.cur[0], c->sort_mst[s], c->sort_dest[s], perm);
         FFPIC_LAUNCH_CHECK();
         place_by_push(c, s);
         c->sort_cur[s] = 1 - t;
@@ -997,7 +1004,7 @@ void sort_species(const SortItem *items, int n, hipStream_t st, bool defer) {
         const int s = items[k].s;
         if (c->sp[s].nub == 0) continue;
         if (bucket_sort_ok(c, s)) small.push_back(items[k]);
-        else if (c->sort_valid[s] && c->incremental_sort) sort_incremental(c, s, defer && !c->fp64);
+        else if (c->sort_valid[s] && c->incremental_sort) sort_incremental(c, s, defer);
         else sort_full(c, s);
     }
     if (!small.empty()) sort_bucketed(small.data(), (int)small.size(), st, defer);

@@ -315,8 +315,9 @@ __global__ void __launch_bounds__(256) k_bucket_place(const BucketArgs P) {
     }
 }
 
-// FP32, for a push that places the sort: the place of the particle in every
-// slot, -1 for a slot that holds no particle of the new order
+// For a push that places the sort: the place of the particle in every slot, -1
+// for a slot that holds no particle of the new order
+template <bool FP64>
 __global__ void __launch_bounds__(256) k_bucket_dest(const BucketArgs P) {
     const BucketJob &J = P.job[blockIdx.y];
     const int q0 = (int)blockIdx.x * 512 + threadIdx.x;
@@ -324,7 +325,10 @@ __global__ void __launch_bounds__(256) k_bucket_dest(const BucketArgs P) {
     const ClassView V = bucket_view(J);
     int c[2];
 #pragma unroll
-    for (int k = 0; k < 2; k++) c[k] = q0 + k * 256 < V.nub ? J.A.cell[q0 + k * 256] : -1;
+    for (int k = 0; k < 2; k++) {
+        const int q = q0 + k * 256;
+        c[k] = q < V.nub ? (FP64 ? (int)J.A.keys[q] : J.A.cell[q]) : -1;
+    }
 #pragma unroll
     for (int k = 0; k < 2; k++) {
         const int q = q0 + k * 256;
@@ -333,7 +337,9 @@ __global__ void __launch_bounds__(256) k_bucket_dest(const BucketArgs P) {
         const bool stay = V.smask[q >> 6] & bit, move = V.mmask[q >> 6] & bit;
         int32_t d = -1;
         if (stay || move) {
-            const uint32_t key = (uint32_t)(c[k] >> 16) * (uint32_t)J.A.nth + (uint32_t)(c[k] & 0xffff);
+            const uint32_t key = FP64 ? (uint32_t)c[k]
+                                      : (uint32_t)(c[k] >> 16) * (uint32_t)J.A.nth +
+                                            (uint32_t)(c[k] & 0xffff);
             d = (int32_t)(stay ? stayers_before(V, q) + (uint32_t)J.mst[key]
                                : mover_place(J, V, key, q));
             if (J.perm) J.perm[d] = q;
@@ -442,7 +448,7 @@ static BucketJob bucket_job(ffpic_ctx *c, int s, bool defer) {
 }
 
 // sorts n species (each with bucket_sort_ok, all FP64 or all FP32) on stream
-// st; with defer (FP32) their next pushes place the particles
+// st; with defer their next pushes place the particles
 void sort_bucketed(const SortItem *items, int n, hipStream_t st, bool defer) {
     for (int i0 = 0; i0 < n; i0 += kBucketJobs) {
         const int m = std::min(n - i0, kBucketJobs);
@@ -461,12 +467,13 @@ void sort_bucketed(const SortItem *items, int n, hipStream_t st, bool defer) {
             hipLaunchKernelGGL(k_bucket_classify<true>, tiles, wide, 0, st, P);
             hipLaunchKernelGGL(k_bucket_keys, dim3(nbk, m), blk, 0, st, P);
             hipLaunchKernelGGL(k_bucket_fill<true>, tiles, wide, 0, st, P);
-            hipLaunchKernelGGL((k_bucket_place<uint64_t, 5, true>), place, blk, 0, st, P);
+            if (defer) hipLaunchKernelGGL(k_bucket_dest<true>, place, blk, 0, st, P);
+            else hipLaunchKernelGGL((k_bucket_place<uint64_t, 5, true>), place, blk, 0, st, P);
         } else {
             hipLaunchKernelGGL(k_bucket_classify<false>, tiles, wide, 0, st, P);
             hipLaunchKernelGGL(k_bucket_keys, dim3(nbk, m), blk, 0, st, P);
             hipLaunchKernelGGL(k_bucket_fill<false>, tiles, wide, 0, st, P);
-            if (defer) hipLaunchKernelGGL(k_bucket_dest, place, blk, 0, st, P);
+            if (defer) hipLaunchKernelGGL(k_bucket_dest<false>, place, blk, 0, st, P);
             else hipLaunchKernelGGL((k_bucket_place<uint32_t, 6, false>), place, blk, 0, st, P);
         }
         FFPIC_LAUNCH_CHECK();
@@ -475,7 +482,7 @@ void sort_bucketed(const SortItem *items, int n, hipStream_t st, bool defer) {
             const int s = items[i0 + k].s;
             ffpic::Species &S = c->sp[s];
             c->sort_cur[s] = 1 - c->sort_cur[s];
-            if (defer && !fp64) {
+            if (defer) {
                 place_by_push(c, s);
             } else {
                 for (int a = 0; a < S.narr; a++) std::swap(S.cur[a], S.alt[a]);

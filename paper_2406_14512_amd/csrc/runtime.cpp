@@ -18,8 +18,8 @@ void field_step64(ffpic_ctx *c);
 void field_step32(ffpic_ctx *c);
 void psi_mask64(ffpic_ctx *c);
 void psi_mask32(ffpic_ctx *c);
-void push64(ffpic_ctx *c, int s);
-void push32(ffpic_ctx *c, int s);
+void push64(ffpic_ctx *c);
+void push32(ffpic_ctx *c);
 
 template <typename R>
 static Geo<R> make_geo(const ffpic_ctx *c, R *const *t) {
@@ -40,7 +40,15 @@ Geo<float> geo<float>(const ffpic_ctx *c) { return make_geo<float>(c, (float *co
 
 void psi_mask(ffpic_ctx *c) { c->fp64 ? psi_mask64(c) : psi_mask32(c); }
 void field_step(ffpic_ctx *c) { c->fp64 ? field_step64(c) : field_step32(c); }
-void push_species(ffpic_ctx *c, int s) { c->fp64 ? push64(c, s) : push32(c, s); }
+void push_all(ffpic_ctx *c) { c->fp64 ? push64(c) : push32(c); }
+
+void after_push(ffpic_ctx *c, int s) {
+    ffpic::Species &S = c->sp[s];
+    if (c->sort_pending[s]) {
+        for (int a = 0; a < S.narr; a++) std::swap(S.cur[a], S.alt[a]);
+        c->sort_pending[s] = false;
+    }
+}
 }  // namespace ffpic
 
 using namespace ffpic;
@@ -535,10 +543,10 @@ void one_step(ffpic_ctx *c, uint32_t ph, bool count_step, int tslot) {
     mark(0);
     if (ph & FFPIC_PHASE_MASK) psi_mask(c);
     mark(1);
-    // FP32: when this step pushes and nothing is appended between the sort
-    // and the push, the push writes its particles in the sorted order (one
-    // pass over the state instead of two)
-    const bool defer = (ph & FFPIC_PHASE_PUSH) && !c->fp64 &&
+    // when this step pushes and nothing is appended between the sort and the
+    // push, the push writes its particles in the sorted order (one pass over
+    // the state instead of two)
+    const bool defer = (ph & FFPIC_PHASE_PUSH) &&
                        !((ph & FFPIC_PHASE_INJECT) && c->d.inject_kappa > 0.0) &&
                        !((ph & FFPIC_PHASE_EXTRACT) && c->d.gj_extract > 0.0);
     SortItem items[FFPIC_MAX_SPECIES];
@@ -558,8 +566,7 @@ void one_step(ffpic_ctx *c, uint32_t ph, bool count_step, int tslot) {
     if (ph & FFPIC_PHASE_INJECT) inject_pairs(c);
     if (ph & FFPIC_PHASE_EXTRACT) extract_gj(c);
     mark(2);
-    if (ph & FFPIC_PHASE_PUSH)
-        for (int s = 0; s < c->d.nspec; s++) push_species(c, s);
+    if (ph & FFPIC_PHASE_PUSH) push_all(c);
     if (ph & FFPIC_PHASE_PAIRS) create_pairs(c);
     mark(3);
     if (ph & FFPIC_PHASE_FIELDS) field_step(c);
