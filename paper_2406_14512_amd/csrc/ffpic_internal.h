@@ -75,6 +75,7 @@ struct CycleState {
     bool sort_valid[FFPIC_MAX_SPECIES], perm_valid[FFPIC_MAX_SPECIES];
     void *E[3], *B[3], *J[3], *dE[3], *dB[3], *stAlt[6], *Jalt[3];
     int fused_rows, push_ppt;        // settings the launches depend on
+    int rates, rb_row0;              // FP32: background rates the field step reads
     bool record_perm, incremental_sort;
 };
 
@@ -109,6 +110,7 @@ struct ffpic_ctx {
     // accumulators for the next push; the pointers swap after each step
     void *stAlt[6] = {}, *Jalt[3] = {};
     bool rE0_zero[3] = {}, rB0_zero[3] = {};  // FP32: background rate identically zero
+    int rb_row0 = 0;                          // FP32: first row with a Faraday rate
     int fused_rows = 0;                       // slab height (0 = from fused_slots)
     int push_ppt = 16;                        // FP32 push: particles per thread (8, 16, 32)
     int fused_slots = 0;                      // workgroups resident on the GPU at once

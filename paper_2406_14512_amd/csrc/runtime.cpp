@@ -362,6 +362,18 @@ void upload_background(ffpic_ctx *c) {
         c->rB0_zero[k] = std::all_of(rB[k].begin(), rB[k].end(),
                                      [&](double v) { return std::fabs(v) <= rb_floor; });
     }
+    // The same row by row: the Faraday rate of a corotating background is zero
+    // but at the outer boundary, where E_theta ends; the rows before the first
+    // with a rate are zero and read as one (see F32Args::rb_row).
+    c->rb_row0 = 0;
+    for (size_t q = 0; c->rb_row0 < nr; c->rb_row0++, q += ld) {
+        bool any = false;
+        for (int k = 0; k < 3 && !any; k++)
+            any = std::any_of(rB[k].begin() + q, rB[k].begin() + q + ld,
+                              [&](double v) { return !(std::fabs(v) <= rb_floor); });
+        if (any) break;
+        for (int k = 0; k < 3; k++) std::fill_n(rB[k].begin() + q, ld, 0.0);
+    }
     auto up = [&](void *dst, const std::vector<double> &h) {
         std::vector<float> f(h.begin(), h.end());
         HCHK(hipMemcpy(dst, f.data(), f.size() * sizeof(float), hipMemcpyHostToDevice));
@@ -608,6 +620,8 @@ CycleState cycle_state(const ffpic_ctx *c) {
     for (int k = 0; k < 6; k++) st.stAlt[k] = c->stAlt[k];
     st.fused_rows = c->fused_rows;
     st.push_ppt = c->push_ppt;
+    for (int k = 0; k < 3; k++) st.rates |= (c->rE0_zero[k] ? 0 : 1 << k) | (c->rB0_zero[k] ? 0 : 8 << k);
+    st.rb_row0 = c->rb_row0;
     st.record_perm = c->record_perm;
     st.incremental_sort = c->incremental_sort;
     return st;
