@@ -927,10 +927,11 @@ int push_key_index(const PushKey &k) { return (k.shell ? 1 : 0) + (k.place ? 2 :
 //   4.0e6   109     82.1   73.6   77.3   90.0
 //   1.0e7   257    180    151    146    157
 //   2.0e7   509    349    283    268    270
+//   2.8e7  1332    737    508    480    508   (16 systems of a batch)
 //   5.0e7  1199    812    664    616    593
 int push_ppt(int setting, int64_t slots) {
     const int64_t rounds = slots / kWG;
-    const int most = rounds < 1536 ? 1 : rounds < 4096 ? 2 : rounds < 24576 ? 4 : rounds < 98304 ? 8 : 32;
+    const int most = rounds < 1536 ? 1 : rounds < 4096 ? 2 : rounds < 24576 ? 4 : rounds < 131072 ? 8 : 32;
     return std::min(setting, most);
 }
 
@@ -989,7 +990,7 @@ using PushGroupKern = void (*)(const PushJob *, const int *, int, int *);
 
 void push32(ffpic_ctx *c) {
     // the species whose kernel is the same share a launch: side by side they
-    // fill the GPU, and its last round, better (two of 6.5e5: 2 x 15 -> 22 us)
+    // fill the GPU, and its last round, better (two of 6.5e5: 2 x 15 -> 24 us)
     bool done[FFPIC_MAX_SPECIES] = {};
     for (int s0 = 0; s0 < c->d.nspec; s0++) {
         if (done[s0] || c->sp[s0].nub == 0) continue;
