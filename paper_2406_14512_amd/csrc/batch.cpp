@@ -219,15 +219,14 @@ struct Group {
 size_t table_bound(const ffpic_batch *b, int steps) {
     size_t n = b->ctx.size(), sp = 0;
     for (const ffpic_ctx *c : b->ctx) sp += (size_t)c->d.nspec;
-    // per step: two tables (jobs, first items) for each of the flux, mask,
+    // per step: two tables (jobs, first items) for each of the flux (and mask),
     // up to kPushKeys push and up to 8 field launches, each array starting at a
     // 256-byte boundary
     const size_t pad = 256;
     const size_t psi = n * ffpic::psi_job_bytes() + (n + 1) * 4 + 2 * pad;
-    const size_t mask = n * ffpic::mask_job_bytes() + (n + 1) * 4 + 2 * pad;
     const size_t push = sp * ffpic::push_job_bytes() + (sp + ffpic::kPushKeys) * 4 + 2 * ffpic::kPushKeys * pad;
     const size_t field = n * ffpic::field_job_bytes() + (n + 8) * 4 + 16 * pad;
-    return (size_t)steps * (psi + mask + push + field) + pad;
+    return (size_t)steps * (psi + push + field) + pad;
 }
 
 void grouped_setup(ffpic_batch *b) {
@@ -250,23 +249,18 @@ void grouped_step(ffpic_batch *b, hipStream_t st, Tables &T) {
     int *ctr = b->gctr;
     const std::vector<ffpic_ctx *> &sys = b->ctx;
     const int n = (int)sys.size();
-    std::vector<char> tmp(std::max({ffpic::psi_job_bytes(), ffpic::mask_job_bytes(),
+    std::vector<char> tmp(std::max({ffpic::psi_job_bytes(),
                                     ffpic::push_job_bytes(), ffpic::field_job_bytes()}));
-    Group psi, mask;
+    Group psi;
     for (ffpic_ctx *c : sys) {
-        int m = ffpic::psi_job32(c, tmp.data());
+        const int m = ffpic::psi_job32(c, tmp.data());
         psi.jobs.insert(psi.jobs.end(), tmp.begin(), tmp.begin() + ffpic::psi_job_bytes());
         psi.starts.push_back(psi.items() + m);
-        m = ffpic::mask_job32(c, tmp.data());
-        mask.jobs.insert(mask.jobs.end(), tmp.begin(), tmp.begin() + ffpic::mask_job_bytes());
-        mask.starts.push_back(mask.items() + m);
     }
     {
-        auto t = psi.place(T);
+        const auto t = psi.place(T);
         ffpic::psi_group_launch(st, t.first, t.second, n, std::min(psi.items(), b->psi_slots),
                                 ctr);
-        t = mask.place(T);
-        ffpic::mask_group_launch(st, t.first, t.second, n, std::min(mask.items(), 4096));
     }
     // each sorting system's launches on its stream's branch (shared by the
     // stream's systems where they are small), so that the sorts of different

@@ -310,13 +310,10 @@ int field_group_slots(int key);
 void field_group_launch(hipStream_t st, int key, const void *jobs, const int *starts, int njobs,
                         int grid, int *ctr);
 size_t psi_job_bytes();
-size_t mask_job_bytes();
 int psi_job32(const ffpic_ctx *c, void *out);
-int mask_job32(const ffpic_ctx *c, void *out);
 int psi_group_slots();
 void psi_group_launch(hipStream_t st, const void *jobs, const int *starts, int njobs, int grid,
                       int *ctr);
-void mask_group_launch(hipStream_t st, const void *jobs, const int *starts, int njobs, int grid);
 
 }  // namespace ffpic
 

@@ -1,4 +1,4 @@
-// Flux function and mask kernels, and the force-free node correction,
+// Flux function and mask kernel, and the force-free node correction,
 // templated on the working precision R.  Included (through fields_fused.h)
 // by k_fields64.hip (compiled without FP contraction, so the FP64 path
 // rounds every product and sum as written) and by k_fields32.hip.
@@ -14,13 +14,24 @@ namespace ffpic {
 // ---------------------------------------------------------------------------
 // eq. (psi): Psi(i, 0) = 0, Psi(i, j+1) = Psi(i, j) + B_r(i, j+1/2) A_r(i, j)
 // with A_r = r_i^2 (cos theta_j - cos theta_{j+1}); FP64, sequential in j so
-// that the rounding is fixed.  A workgroup owns kPsiRows radial rows and
+// that the rounding is fixed.  A workgroup takes ROWS radial rows and
 // walks them in tiles of kPsiCols columns: all 256 threads load a tile with
 // coalesced reads along theta and form its terms B_r A_r in parallel (each
 // product rounded as in the serial form) into LDS, then one lane per row
 // runs the serial sum over the tile while the next tile's loads are in
-// flight, and the tile of partial sums is written back coalesced.
-constexpr int kPsiRows = 16;
+// flight, and the tile of partial sums is written back coalesced, with the
+// blending function f at its nodes (eq. transition, four thresholds) and the
+// kill flag of each cell whose four corners have f = 1.  A cell needs the row
+// above it, so the blocks overlap by one row, which the next block writes.
+//
+// Rows: few while the blocks do not fill the GPU, more where the overlap is
+// traffic.  us with 4, 8 and 16 rows, and with 16 and the mask in a kernel of
+// its own, which read Psi back:
+//   128^2 FP64          5.4    6.5    9.1    11.7
+//   300 x 517 FP32     12.8   15.7   23.5    18.9
+//   1024^2 FP32        22.9   25.7           28.3
+//   4096^2 FP32       153    116    128     130
+//   16 systems        138    116     87      98    (one launch, 6e6 nodes)
 constexpr int kPsiCols = 256;
 constexpr int kPsiRun = 32;     // terms a lane sums between LDS reads
 
@@ -31,45 +42,69 @@ __device__ __forceinline__ void lds_barrier() {
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
-// the arguments of one system's flux function
+// the arguments of one system's flux function and mask
 template <typename R>
 struct PsiJob {
-    int nr, nth, ld;
-    int blocks;                // workgroups of kPsiRows rows
+    int nr, nth, ld, ff;
+    int blocks;                // workgroups of ROWS rows, ROWS - 1 apart
     const double *rn2, *dcn;   // r_i^2, cos theta_j - cos theta_{j+1}
+    double t0, t1, t2, t3;
     const R *br;
     double *psi;
+    R *f;
+    uint8_t *kill;
 };
 
-// rows [bx * kPsiRows, ...) of one system; every thread of the workgroup
+constexpr int kPsiGroupRows = 16;
+inline int psi_rows(int nr) { return nr < 2048 ? 4 : 8; }
+
+template <int ROWS>
+struct PsiSmem {
+    double tile[ROWS][kPsiCols + 1];
+    uint32_t one[kPsiCols + 1];   // per column, bit rr: f = 1 in row rr
+};
+
+// rows [bx * (ROWS - 1), ...) of one system; every thread of the workgroup
 // calls it and returns from it together
-template <typename R>
-__device__ __forceinline__ void psi_block(const PsiJob<R> &P, int bx,
-                                          double (*tile)[kPsiCols + 1]) {
+template <typename R, int ROWS>
+__device__ __forceinline__ void psi_block(const PsiJob<R> &P, int bx, PsiSmem<ROWS> &L) {
+    constexpr int OWN = ROWS - 1;   // rows a block writes (the last: all of its own)
+    auto &tile = L.tile;
     const int t = threadIdx.x;
-    const int i0 = bx * kPsiRows;
+    const int i0 = bx * OWN;
     const int ld = P.ld, nr = P.nr, nth = P.nth;
     const R *__restrict__ br = P.br;
     double *__restrict__ psi = P.psi;
-    const int rows = min(kPsiRows, nr + 1 - i0);
-    double r2[kPsiRows];
+    R *__restrict__ f = P.f;
+    uint8_t *__restrict__ kill = P.kill;
+    const int rows = min(ROWS, nr + 1 - i0);
+    const int own = i0 + OWN < nr ? OWN : rows;   // rows written
+    const int cells = min(own, nr - i0);                  // rows of cells
+    auto fval = [&](double v) { return P.ff ? blend(v, P.t0, P.t1, P.t2, P.t3) : 0.0; };
+    // the column before the tile: Psi = 0 on the axis
+    const double f0 = fval(0.0);
+    if (t == 0) L.one[0] = f0 == 1.0 ? ~0u : 0u;
+    double r2[ROWS];
 #pragma unroll
-    for (int rr = 0; rr < kPsiRows; rr++) r2[rr] = rr < rows ? P.rn2[i0 + rr] : 0.0;
+    for (int rr = 0; rr < ROWS; rr++) r2[rr] = rr < rows ? P.rn2[i0 + rr] : 0.0;
     double acc = 0.0;
-    if (t < rows) psi[ix(ld, i0 + t, 0)] = 0.0;
+    if (t < own) {
+        psi[ix(ld, i0 + t, 0)] = 0.0;
+        f[ix(ld, i0 + t, 0)] = (R)f0;
+    }
     // The tile's B_r and column areas are loaded one tile ahead.
-    R nxt[kPsiRows];
+    R nxt[ROWS];
     double arn;
     auto load = [&](int jt) {
         arn = jt + t < nth ? P.dcn[jt + t] : 0.0;
 #pragma unroll
-        for (int rr = 0; rr < kPsiRows; rr++)
+        for (int rr = 0; rr < ROWS; rr++)
             nxt[rr] = (rr < rows && jt + t < nth) ? br[ix(ld, i0 + rr, jt + t)] : (R)0;
     };
     // the tile's terms B_r A_r, each product rounded as in the serial form
     auto terms = [&]() {
 #pragma unroll
-        for (int rr = 0; rr < kPsiRows; rr++) {
+        for (int rr = 0; rr < ROWS; rr++) {
 #pragma clang fp contract(off)
             tile[rr][t] = (double)nxt[rr] * (r2[rr] * arn);
         }
@@ -113,74 +148,44 @@ __device__ __forceinline__ void psi_block(const PsiJob<R> &P, int bx,
         // still in flight, and the wait for the next tile's loads does not
         // also wait for this write-back
         const int tc = min(t, w - 1);
+        uint32_t one = 0;
 #pragma unroll
-        for (int rr = 0; rr < kPsiRows; rr++) {
-            const int rc = min(rr, rows - 1);
-            psi[ix(ld, i0 + rc, j0 + 1 + tc)] = tile[rc][tc];
+        for (int rr = 0; rr < ROWS; rr++) {
+            const double v = tile[rr][tc], fv = fval(v);
+            one |= (fv == 1.0 ? 1u : 0u) << rr;
+            const size_t k = ix(ld, i0 + min(rr, own - 1), j0 + 1 + tc);
+            const double vw = rr < own ? v : tile[own - 1][tc];
+            psi[k] = vw;
+            f[k] = (R)(rr < own ? fv : fval(vw));
         }
+        if (t < w) L.one[t + 1] = one;
         lds_barrier();
+        // cells of column j0 + t: both columns' flags, and those of the row above
+        const uint32_t both = L.one[tc] & L.one[tc + 1], dead = both & (both >> 1);
+        const uint32_t last = L.one[w];
+#pragma unroll
+        for (int rr = 0; rr < OWN; rr++)
+            if (t < w && rr < cells) kill[(size_t)(i0 + rr) * nth + j0 + t] = (dead >> rr) & 1u;
+        lds_barrier();
+        if (t == 0) L.one[0] = last;
         if (jn < nth) terms();
     }
 }
 
-template <typename R>
+template <typename R, int ROWS>
 __global__ void __launch_bounds__(kPsiCols) k_psi(const PsiJob<R> P) {
-    __shared__ double tile[kPsiRows][kPsiCols + 1];
-    psi_block<R>(P, (int)blockIdx.x, tile);
+    __shared__ PsiSmem<ROWS> L;
+    psi_block<R, ROWS>(P, (int)blockIdx.x, L);
 }
 
-// the arguments of one system's mask
-template <typename R>
-struct MaskJob {
-    int nr, nth, ld, ff;
-    int cblocks;               // workgroups of 256 columns per row
-    double t0, t1, t2, t3;
-    const double *psi;
-    R *f;
-    uint8_t *kill;
-};
-
-// blending function f at nodes (eq. transition, four thresholds) and the
-// kill flag of each cell (all four corners at f = 1): columns from bx * 256
-// of row i
-template <typename R>
-__device__ __forceinline__ void mask_row(const MaskJob<R> &M, int bx, int i) {
-    const int j = bx * 256 + (int)threadIdx.x;
-    const int nr = M.nr, nth = M.nth, ld = M.ld;
-    if (j > nth) return;
-    const double t0 = M.t0, t1 = M.t1, t2 = M.t2, t3 = M.t3;
-    const double *__restrict__ psi = M.psi;
-    // the node and its three neighbours towards the cell's far corner are
-    // loaded together (the last row and column read their own node again):
-    // behind a branch each, the compiler would wait for one after the other
-    const bool cell = i < nr && j < nth;
-    const int i1 = cell ? i + 1 : i, j1 = cell ? j + 1 : j;
-    const double p00 = psi[ix(ld, i, j)], p10 = psi[ix(ld, i1, j)];
-    const double p01 = psi[ix(ld, i, j1)], p11 = psi[ix(ld, i1, j1)];
-    const double fv = M.ff ? blend(p00, t0, t1, t2, t3) : 0.0;
-    M.f[ix(ld, i, j)] = (R)fv;
-    if (cell) {
-        const bool k = M.ff && fv == 1.0 && blend(p10, t0, t1, t2, t3) == 1.0 &&
-                       blend(p01, t0, t1, t2, t3) == 1.0 && blend(p11, t0, t1, t2, t3) == 1.0;
-        M.kill[(size_t)i * nth + j] = k ? 1 : 0;
-    }
-}
-
-template <typename R>
-__global__ void __launch_bounds__(256) k_mask(const MaskJob<R> M) {
-    mask_row<R>(M, (int)blockIdx.x, (int)blockIdx.y);
-}
-
-// The flux functions of many systems in one launch of persistent
+// The flux functions and masks of many systems in one launch of persistent
 // workgroups taking row blocks from a counter (job k owns items
-// [starts[k], starts[k + 1])), and their masks in a second launch whose
-// workgroups stride over (system, row) items: a mask row is a few kB of
-// streaming, too little to be worth a counter.
+// [starts[k], starts[k + 1])).
 template <typename R>
 __global__ void __launch_bounds__(kPsiCols) k_psi_group(const PsiJob<R> *__restrict__ jobs,
                                                         const int *__restrict__ starts,
                                                         int njobs, int *__restrict__ ctr) {
-    __shared__ double tile[kPsiRows][kPsiCols + 1];
+    __shared__ PsiSmem<kPsiGroupRows> L;
     __shared__ int next, job;
     __shared__ uint32_t stage[kJobWords];
     const int total = starts[njobs];
@@ -193,28 +198,12 @@ __global__ void __launch_bounds__(kPsiCols) k_psi_group(const PsiJob<R> *__restr
         if (threadIdx.x == 0) nx = atomicAdd(&ctr[0], 1);
         __syncthreads();
         const int lo = __builtin_amdgcn_readfirstlane(job);
-        psi_block<R>(stage_uniform(jobs + lo, stage), item - starts[lo], tile);
+        psi_block<R, kPsiGroupRows>(stage_uniform(jobs + lo, stage), item - starts[lo], L);
         if (threadIdx.x == 0) next = nx;
         __syncthreads();
         item = __builtin_amdgcn_readfirstlane(next);
     }
     group_done(ctr);
-}
-
-template <typename R>
-__global__ void __launch_bounds__(256) k_mask_group(const MaskJob<R> *__restrict__ jobs,
-                                                    const int *__restrict__ starts, int njobs) {
-    __shared__ int job;
-    const int total = starts[njobs];
-    for (int item = (int)blockIdx.x; item < total; item += (int)gridDim.x) {
-        find_job(starts, njobs, item, &job);
-        __syncthreads();
-        const int lo = __builtin_amdgcn_readfirstlane(job);
-        const MaskJob<R> &M = jobs[lo];
-        const int i = item - starts[lo];
-        for (int bx = 0; bx < M.cblocks; bx++) mask_row<R>(M, bx, i);
-        __syncthreads();               // job is rewritten for the next item
-    }
 }
 
 // force-free correction at a node: E.B projection then the |E| <= |B| cap
@@ -240,37 +229,28 @@ __device__ __forceinline__ void ff_node(const double e[3], const double b[3], do
 }
 
 template <typename R>
-PsiJob<R> psi_job(const ffpic_ctx *c) {
+PsiJob<R> psi_job(const ffpic_ctx *c, int rows) {
     PsiJob<R> P;
     P.nr = c->nr; P.nth = c->nth; P.ld = c->ld;
-    P.blocks = (c->nr + 1 + kPsiRows - 1) / kPsiRows;
+    P.ff = c->d.ff_enable ? 1 : 0;
+    P.blocks = (c->nr + rows - 2) / (rows - 1);
     P.rn2 = c->dtab64[T_RN2];
     P.dcn = c->dtab64[T_DCN];
     P.br = (const R *)c->B[0];
     P.psi = c->psi;
+    const double *t = c->d.psi_thr;
+    P.t0 = t[0]; P.t1 = t[1]; P.t2 = t[2]; P.t3 = t[3];
+    P.f = (R *)c->f;
+    P.kill = c->kill;
     return P;
 }
 
 template <typename R>
-MaskJob<R> mask_job(const ffpic_ctx *c) {
-    MaskJob<R> M;
-    M.nr = c->nr; M.nth = c->nth; M.ld = c->ld;
-    M.ff = c->d.ff_enable ? 1 : 0;
-    M.cblocks = (c->nth + 1 + 255) / 256;
-    const double *t = c->d.psi_thr;
-    M.t0 = t[0]; M.t1 = t[1]; M.t2 = t[2]; M.t3 = t[3];
-    M.psi = c->psi;
-    M.f = (R *)c->f;
-    M.kill = c->kill;
-    return M;
-}
-
-template <typename R>
 static void run_psi_mask(ffpic_ctx *c) {
-    const PsiJob<R> P = psi_job<R>(c);
-    hipLaunchKernelGGL(k_psi<R>, dim3(P.blocks), dim3(kPsiCols), 0, c->stream, P);
-    const MaskJob<R> M = mask_job<R>(c);
-    hipLaunchKernelGGL(k_mask<R>, dim3(M.cblocks, c->nr + 1), dim3(256), 0, c->stream, M);
+    const int rows = psi_rows(c->nr);
+    const PsiJob<R> P = psi_job<R>(c, rows);
+    auto kern = rows == 4 ? k_psi<R, 4> : k_psi<R, 8>;
+    hipLaunchKernelGGL(kern, dim3(P.blocks), dim3(kPsiCols), 0, c->stream, P);
     FFPIC_LAUNCH_CHECK();
 }
 

@@ -91,18 +91,11 @@ void field_group_launch(hipStream_t st, int key, const void *jobs, const int *st
 }
 
 size_t psi_job_bytes() { return sizeof(PsiJob<float>); }
-size_t mask_job_bytes() { return sizeof(MaskJob<float>); }
 
 int psi_job32(const ffpic_ctx *c, void *out) {
-    const PsiJob<float> P = psi_job<float>(c);
+    const PsiJob<float> P = psi_job<float>(c, kPsiGroupRows);
     std::memcpy(out, &P, sizeof(P));
     return P.blocks;
-}
-
-int mask_job32(const ffpic_ctx *c, void *out) {
-    const MaskJob<float> M = mask_job<float>(c);
-    std::memcpy(out, &M, sizeof(M));
-    return c->nr + 1;
 }
 
 int psi_group_slots() { return occupancy_slots((const void *)k_psi_group<float>, kPsiCols, 4); }
@@ -114,9 +107,4 @@ void psi_group_launch(hipStream_t st, const void *jobs, const int *starts, int n
     FFPIC_LAUNCH_CHECK();
 }
 
-void mask_group_launch(hipStream_t st, const void *jobs, const int *starts, int njobs, int grid) {
-    hipLaunchKernelGGL(k_mask_group<float>, dim3(grid), dim3(256), 0, st,
-                       (const MaskJob<float> *)jobs, starts, njobs);
-    FFPIC_LAUNCH_CHECK();
-}
 }  // namespace ffpic
