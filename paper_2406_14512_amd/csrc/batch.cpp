@@ -303,12 +303,14 @@ void grouped_step(ffpic_batch *b, hipStream_t st, Tables &T) {
                                  std::min(push[k].items(), b->push_slots[k]), ctr);
     }
     // one slab height for all systems: enough items to fill the GPU once, in
-    // slabs of at most 32 rows (finer items balance the persistent workgroups)
-    // and at least 8 (the systems fill the GPU together, so halo rows cost)
+    // slabs of at most 16 rows (finer items balance the persistent workgroups:
+    // 16 systems of 6e6 nodes 353, 349, 353, 372 and 476 us with 12, 16, 24, 32
+    // and 64 rows) and at least 8 (the systems fill the GPU together, so halo
+    // rows cost)
     Group field[8];
     int64_t strip_rows = 0;
     for (ffpic_ctx *c : sys) strip_rows += (int64_t)ffpic::field_strips(c) * (c->nr + 1);
-    const int rows = (int)std::clamp<int64_t>(strip_rows / std::max(1, b->field_slots[5]), 8, 32);
+    const int rows = (int)std::clamp<int64_t>(strip_rows / std::max(1, b->field_slots[5]), 8, 16);
     for (ffpic_ctx *c : sys) {
         int key = 0;
         const int m = ffpic::field_job(c, tmp.data(), &key, rows);

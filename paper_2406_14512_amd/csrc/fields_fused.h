@@ -25,8 +25,8 @@
 // node quantities (J_FFE, the correction) use the totals F0 + dF, which the
 // FP32 step also writes for the particle gather.
 //
-// Tiling.  A workgroup owns a strip of kFzW theta columns (plus kFzL halo
-// columns before and kFzR after, one thread per column) and a slab of
+// Tiling.  A workgroup owns a strip of theta columns (plus kFzL halo columns
+// before and kFzR after, one thread per column) and a slab of
 // `rows` radial rows, and marches through the slab row by row, keeping the
 // recent rows of each stage in registers (its own column) and in small
 // LDS rings (the theta neighbours).  At iteration q it loads row q and
@@ -112,16 +112,17 @@ __device__ __forceinline__ void ff_node_f(const float e[3], const float b[3], fl
     }
 }
 
-template <bool FF>
-__global__ void __launch_bounds__(kFzT) k_field_fused(const FusedArgs A) {
+template <bool FF, int T>
+__global__ void __launch_bounds__(T) k_field_fused(const FusedArgs A) {
+    constexpr int W = T - kFzL - kFzR;   // owned columns
     using R = double;
     const Geo<R> &g = A.g;
     const int nr = g.nr, nth = g.nth, ld = g.ld;
     const int t = threadIdx.x;
-    const int j = (int)blockIdx.x * kFzW + t - kFzL;
+    const int j = (int)blockIdx.x * W + t - kFzL;
     const bool colok = j >= 0 && j <= nth;
     const int jc = min(max(j, 0), nth);
-    const int tl = t > 0 ? t - 1 : t, tr = t < kFzT - 1 ? t + 1 : t;
+    const int tl = t > 0 ? t - 1 : t, tr = t < T - 1 ? t + 1 : t;
     const int i0 = (int)blockIdx.y * A.rows;
     const int iL = min(i0 + A.rows - 1, nr);
     const int qs = max(i0 - 2, 0);
@@ -141,13 +142,13 @@ __global__ void __launch_bounds__(kFzT) k_field_fused(const FusedArgs A) {
             y_dthd = rcp64(dthd_j), y_dth = rcp64(dth), y_dt = rcp64(dt);
 
     // LDS rings (theta neighbours); a ring slot holds one row of one quantity
-    __shared__ R lE[2][3][kFzT];          // E^n: r, phi, theta
-    __shared__ R lB[4][2][kFzT];          // B^{n+1/2}: r, phi
-    __shared__ R lN[FF ? 2 : 1][kFzT];    // J_FFE theta
-    __shared__ R lF[FF ? 3 : 1][kFzT];    // f
-    __shared__ R lEa[FF ? 2 : 1][kFzT];   // E after Ampere, theta
-    __shared__ R lD[FF ? 2 : 1][kFzT];    // delta theta
-    __shared__ R lEf[2][2][kFzT];         // final E: r, phi
+    __shared__ R lE[2][3][T];          // E^n: r, phi, theta
+    __shared__ R lB[4][2][T];          // B^{n+1/2}: r, phi
+    __shared__ R lN[FF ? 2 : 1][T];    // J_FFE theta
+    __shared__ R lF[FF ? 3 : 1][T];    // f
+    __shared__ R lEa[FF ? 2 : 1][T];   // E after Ampere, theta
+    __shared__ R lD[FF ? 2 : 1][T];    // delta theta
+    __shared__ R lEf[2][2][T];         // final E: r, phi
 
     // own-column history (suffix = rows back from the newest loaded row q)
     R sE0[3] = {}, sE1[3] = {}, sE2[3] = {};        // E state rows q, q-1, q-2
@@ -465,7 +466,7 @@ __global__ void __launch_bounds__(kFzT) k_field_fused(const FusedArgs A) {
                     }
                 }
             }
-            if (t >= kFzL && t < kFzL + kFzW && colok) {
+            if (t >= kFzL && t < kFzL + W && colok) {
                 const size_t k0 = ix(ld, fr, 0);
                 const unsigned jk = jc;
 #pragma unroll
@@ -506,10 +507,10 @@ __global__ void __launch_bounds__(kFzT) k_field_fused(const FusedArgs A) {
 // (FP64 before its rows were loaded ahead); from 2048^2 on 32 rows or more
 // fill the GPU.  `shared`: the height for a
 // launch that many systems share (0 = this system alone).
-inline int fused_rows(const ffpic_ctx *c, int shared = 0) {
+inline int fused_rows(const ffpic_ctx *c, int width, int shared = 0) {
     if (c->fused_rows > 0) return c->fused_rows;
     if (shared > 0) return shared;
-    const int nbx = (c->nth + 1 + kFzW - 1) / kFzW;
+    const int nbx = (c->nth + 1 + width - 1) / width;
     const int slots = c->fused_slots > 0 ? c->fused_slots : 768;
     const int slabs = std::max(1, slots / nbx);
     return (c->nr + 1 + slabs - 1) / slabs;
@@ -550,6 +551,19 @@ static std::vector<double> fused64_rows(const ffpic_ctx *c) {
     return {p, p + row.size() * (sizeof(FusedRow) / sizeof(double))};
 }
 
+// Threads of a workgroup of the FP64 field step: 128 where its strips cover
+// the columns with fewer threads than those of 256 (a strip costs the same
+// whatever part of it is on the grid), else 256, whose halo is a smaller part.
+// Step without particles, us with 128 and 256: 128^2 17.5 and 19.8, 256^2 21.5
+// and 25.5, 400 x 333 26.6 and 28.5, 1024^2 62 and 66, 2048^2 196 and 206,
+// 3000 x 1500 217 and 232, 4096^2 (4352 threads a row either way) 673 and 655.
+// The FP32 step, which waits for memory more, gains nothing from it (16 systems
+// grouped 376 and 372 us, 4096^2 650 and 619).
+inline int fused_threads64(int nth) {
+    auto threads = [&](int t) { return (nth + t - kFzL - kFzR) / (t - kFzL - kFzR) * t; };
+    return threads(128) < threads(256) ? 128 : 256;
+}
+
 // FP64 field step (E and B evolved directly)
 static void run_field_fused64(ffpic_ctx *c) {
     using R = double;
@@ -566,10 +580,12 @@ static void run_field_fused64(ffpic_ctx *c) {
         A.Jz[k] = (R *)c->Jalt[k];
     }
     A.f = (const R *)c->f;
-    auto kern = c->d.ff_enable ? k_field_fused<true> : k_field_fused<false>;
+    const int T = fused_threads64(c->nth), width = T - kFzL - kFzR;
+    auto kern = T == 128 ? (c->d.ff_enable ? k_field_fused<true, 128> : k_field_fused<false, 128>)
+                         : (c->d.ff_enable ? k_field_fused<true, 256> : k_field_fused<false, 256>);
     if (c->fused_slots == 0) {   // workgroups resident at once, for the slab height
         int per_cu = 0, cus = 0, dev = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)kern, kFzT, 0) !=
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)kern, T, 0) !=
                 hipSuccess ||
             hipGetDevice(&dev) != hipSuccess ||
             hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) {
@@ -579,9 +595,9 @@ static void run_field_fused64(ffpic_ctx *c) {
         }
         c->fused_slots = std::max(1, per_cu * cus);
     }
-    A.rows = fused_rows(c);
-    dim3 grd((c->nth + 1 + kFzW - 1) / kFzW, (c->nr + 1 + A.rows - 1) / A.rows);
-    hipLaunchKernelGGL(kern, grd, dim3(kFzT), 0, c->stream, A);
+    A.rows = fused_rows(c, width);
+    dim3 grd((c->nth + 1 + width - 1) / width, (c->nr + 1 + A.rows - 1) / A.rows);
+    hipLaunchKernelGGL(kern, grd, dim3(T), 0, c->stream, A);
     FFPIC_LAUNCH_CHECK();
     // the new state and the cleared accumulators become current
     for (int k = 0; k < 3; k++) {

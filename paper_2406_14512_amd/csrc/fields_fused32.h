@@ -567,7 +567,7 @@ static F32Args f32_args(ffpic_ctx *c, int shared_rows = 0) {
     A.colc = (const float4 *)c->fz_colc;
     if (c->fused_slots == 0)
         c->fused_slots = occupancy_slots((const void *)f32_kern(f32_key(c, A)), kFzT, 3);
-    A.rows = fused_rows(c, shared_rows);
+    A.rows = fused_rows(c, kFzW, shared_rows);
     return A;
 }
 
