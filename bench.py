@@ -149,8 +149,9 @@ def run_timed(ffpic, sim, steps, warmup, nspec, sort_interval, phase_steps=16):
 
 
 def roofline(precision, res, steps, nspec, copy_gbs):
-    # dominant kernel: the push + deposit kernel, one launch per species and
-    # step; algorithmic bytes = state read + written per live particle.  The
+    # dominant kernel: the push + deposit kernel, whose one launch per step
+    # covers every species; times and bytes per launch are a species' share of
+    # it; algorithmic bytes = state read + written per live particle.  The
     # launch time is that of the plain instance (steps without a sort) where
     # measured; the average over whole sort cycles, which includes the
     # pushes that also place the new order, is reported beside it
@@ -202,7 +203,7 @@ def valu_per_particle(precision):
     path = os.path.join(ROOT, SQ_FILE)
     if not os.path.exists(path):
         return None
-    want = "k_push32<false, 16, false>" if precision == 1 else "k_push64 :"
+    want = "k_push32<false, false>" if precision == 1 else "k_push64<8, true, false>"
     block = False
     with open(path) as fh:
         for line in fh:

@@ -52,8 +52,9 @@
 // comes through the scalar cache.  With the divisions by products of geometry
 // factors taken as products of stored reciprocals, corrected to the rounded
 // quotient, the FP64 step with the force-free stages went from 380 to 206 us
-// at 2048^2 (152 B per node: 3.1 TB/s), from 138 to 77 us at 1024^2; the
-// reciprocals without the loads ahead gave 362 and 119 us.
+// at 2048^2, from 138 to 77 us at 1024^2; the reciprocals without the loads
+// ahead gave 362 and 119 us.  With strips of 128 threads (fused_threads64)
+// 194 and 72 us (152 B per node: 3.3 TB/s at 2048^2).
 #pragma once
 
 #include <algorithm>
