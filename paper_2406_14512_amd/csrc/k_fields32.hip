@@ -98,11 +98,11 @@ int psi_job32(const ffpic_ctx *c, void *out) {
     return P.blocks;
 }
 
-int psi_group_slots() { return occupancy_slots((const void *)k_psi_group<float>, kPsiCols, 4); }
+int psi_group_slots() { return occupancy_slots((const void *)k_psi_group<float>, kPsiThreads, 4); }
 
 void psi_group_launch(hipStream_t st, const void *jobs, const int *starts, int njobs, int grid,
                       int *ctr) {
-    hipLaunchKernelGGL(k_psi_group<float>, dim3(grid), dim3(kPsiCols), 0, st,
+    hipLaunchKernelGGL(k_psi_group<float>, dim3(grid), dim3(kPsiThreads), 0, st,
                        (const PsiJob<float> *)jobs, starts, njobs, ctr);
     FFPIC_LAUNCH_CHECK();
 }

@@ -1,7 +1,7 @@
 """Flux function, blending function and kill flags from one kernel, whose
 blocks overlap by one radial row: grids whose last block holds one row of cells
-or a full set, for the 4 rows of small grids, the 8 of large ones and the 16 of
-grouped launches, and columns around the tile of 256.  The flux function is a
+or a full set, for the 4 to 12 rows of single launches and the 16 of grouped
+ones, and columns around the tile of 256.  The flux function is a
 sum in a fixed order and the rest are choices made from it, so everything is
 bit for bit the oracle's (FP32: the single context's)."""
 import math
@@ -46,6 +46,13 @@ def test_flux_mask_and_kill_flags(nr, nth):
     assert 0 < len(cells) < nr * nth
     assert np.array_equal(cells, ora.particles(0)["cell"])
     assert not kill_cells(sim, nr, nth)[cells].any()
+
+
+@pytest.mark.parametrize("nr,nth", [(768, 20), (769, 20), (771, 600), (1276, 8), (1281, 8),
+                                    (1289, 300), (1793, 6), (1794, 257), (2816, 6), (2817, 6),
+                                    (2824, 260)])
+def test_flux_mask_and_kill_flags_by_rows(nr, nth):
+    test_flux_mask_and_kill_flags(nr, nth)
 
 
 def test_flux_and_mask_grouped():
