@@ -13,6 +13,10 @@ __device__ __forceinline__ size_t ix(int ld, int i, int j) {
     return (size_t)i * (size_t)ld + (size_t)j;
 }
 
+// row of a cell packed as (row << 16) | column: rows go up to 65534, so the
+// packed word may be negative
+__device__ __forceinline__ int cell_row(int c) { return (int)((unsigned)c >> 16); }
+
 // hardware float / double atomic add to global memory, device scope,
 // no return value
 template <typename R>

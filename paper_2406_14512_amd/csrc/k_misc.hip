@@ -340,7 +340,7 @@ k_charge(int nub, const int32_t *__restrict__ nslots, int nr, int nth, int ld, d
         // (a row index above 32767 makes the packed cell negative in FP64
         // only: dead is exactly -1 there, and no cell packs to it)
         if (F64 ? cell[k] != -1 : cell[k] >= 0) {
-            const int i = (int)((unsigned)cell[k] >> 16), j = cell[k] & 0xffff;
+            const int i = cell_row(cell[k]), j = cell[k] & 0xffff;
             imin = min(imin, i); imax = max(imax, i);
             jmin = min(jmin, j); jmax = max(jmax, j);
         }
@@ -392,7 +392,7 @@ k_charge(int nub, const int32_t *__restrict__ nslots, int nr, int nth, int ld, d
             z += dpp_f64<0x124>(z);
             z += dpp_f64<0x128>(z);
             if ((lane & 12) == 0 && rowm != 0u) {
-                const int li = (int)((unsigned)lc >> 16) + kdi, lj = (lc & 0xffff) + kdj;
+                const int li = cell_row(lc) + kdi, lj = (lc & 0xffff) + kdj;
                 if (lds) atomicAdd(&tile[(li - i0) * TJ + lj - j0], z);
                 else gadd(&qn[ix(ld, li, lj)], z);
             }

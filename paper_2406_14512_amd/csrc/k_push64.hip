@@ -662,7 +662,7 @@ __device__ __forceinline__ void push_chunk64(KArgs A0, const Patch64 &F,
                 if (LDS) {
                     atomicAdd(&acc.tile[lc + kofs], v);
                 } else {
-                    gadd(&kg[ix(A->p.ld, (lc >> 16) + kdi, (lc & 0xffff) + kdj)], v);
+                    gadd(&kg[ix(A->p.ld, cell_row(lc) + kdi, (lc & 0xffff) + kdj)], v);
                 }
             }
             pend = pend && !part;
@@ -705,7 +705,7 @@ __device__ __forceinline__ void push_chunk64(KArgs A0, const Patch64 &F,
     const int nq = min(*qn, kQueue64);
     for (int e = tid; e < nq; e += kWG64) {
         const Move64 m = queue[e];
-        zigzag64(A0, acc, m.c >> 16, m.c & 0xffff, (int)(short)(m.d & 0xffff), m.d >> 16, m.x1, m.y1,
+        zigzag64(A0, acc, cell_row(m.c), m.c & 0xffff, (int)(short)(m.d & 0xffff), m.d >> 16, m.x1, m.y1,
                  m.x2, m.y2, m.v1);
     }
 }
