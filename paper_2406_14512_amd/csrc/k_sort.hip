@@ -783,11 +783,14 @@ __global__ void __launch_bounds__(256) k_stayer_dest(ClassView V, int nth,
     const int wbase = __builtin_amdgcn_readfirstlane(
         (int)(blockIdx.x * (256 * kDestSlots) + (threadIdx.x & ~63u)));
     const uint64_t below = (1ull << lane) - 1ull;
+    // (the slots from the device's count to the host's bound hold no cell, and
+    // may never have been written: their key would lie outside the keys)
+    const int ns = min(V.nub, (int)V.tot[2]);
     int c[kDestSlots];
 #pragma unroll
     for (int k = 0; k < kDestSlots; k++) {
         const int q = wbase + k * 256 + lane;
-        c[k] = q < V.nub ? cell[q] : -1;
+        c[k] = q < ns ? cell[q] : -1;
     }
     int32_t ms[kDestSlots];
 #pragma unroll
