@@ -13,9 +13,14 @@ __device__ __forceinline__ size_t ix(int ld, int i, int j) {
     return (size_t)i * (size_t)ld + (size_t)j;
 }
 
-// row of a cell packed as (row << 16) | column: rows go up to 65534, so the
-// packed word may be negative
+// A cell packed as (row << 16) | column.  Rows and columns go up to 65534, so a
+// packed cell may be negative, and -1, which no cell packs to, is a dead slot.
 __device__ __forceinline__ int cell_row(int c) { return (int)((unsigned)c >> 16); }
+__device__ __forceinline__ bool cell_live(int c) { return c != -1; }
+// its sort key: row * nth + column
+__device__ __forceinline__ uint32_t cell_key(int c, int nth) {
+    return ((unsigned)c >> 16) * (unsigned)nth + ((unsigned)c & 0xffffu);
+}
 
 // hardware float / double atomic add to global memory, device scope,
 // no return value

@@ -125,8 +125,8 @@ __global__ void __launch_bounds__(kSpecWG)
                 }
             } else {
                 const int c = ((const int32_t *)s0)[q];
-                if (c >= 0) {
-                    i = c >> 16;
+                if (cell_live(c)) {
+                    i = cell_row(c);
                     j = c & 0xffff;
                     a = (double)((const float *)s1)[q];
                     b = (double)((const float *)s2)[q];

@@ -209,7 +209,7 @@ __global__ void k_surface_count(int nub, const int32_t *__restrict__ nslots, int
         if (i == 0) atomicAdd(&have[j], 1);
     } else {
         const int cell = ((const int32_t *)a0)[q];
-        if (cell >= 0 && (cell >> 16) == 0) atomicAdd(&have[cell & 0xffff], 1);
+        if (cell_live(cell) && cell_row(cell) == 0) atomicAdd(&have[cell & 0xffff], 1);
     }
 }
 

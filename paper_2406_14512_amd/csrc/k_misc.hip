@@ -116,10 +116,10 @@ __global__ void k_export32(int n, int nth, double dlog, double dth, const double
     int q = blockIdx.x * blockDim.x + threadIdx.x;
     if (q >= n) return;
     int c = CELL[q];
-    if (c < 0) {
+    if (!cell_live(c)) {
         r[q] = -1.0; th[q] = 0.0; cell[q] = -1;
     } else {
-        int i = c >> 16, j = c & 0xffff;
+        int i = cell_row(c), j = c & 0xffff;
         r[q] = rn[i] * exp((double)A[q] * dlog);
         th[q] = thn[j] + (double)Bo[q] * dth;
         cell[q] = i * nth + j;
@@ -246,7 +246,7 @@ __global__ void k_moments(int nub, const int32_t *nslots, const void *c0, const 
         for (int k = 0; k < 4; k++) {
             const int64_t qk = (int64_t)q0 + (int64_t)k * stride;
             const int q = (int)min<int64_t>(qk, n - 1);
-            live[k] = (F64 ? ((const double *)c0)[q] > 0.0 : ((const int32_t *)c0)[q] >= 0) && qk < n;
+            live[k] = (F64 ? ((const double *)c0)[q] > 0.0 : cell_live(((const int32_t *)c0)[q])) && qk < n;
             ur[k] = ((const T *)u0)[q]; ut[k] = ((const T *)u1)[q]; up[k] = ((const T *)u2)[q];
         }
 #pragma unroll
@@ -337,9 +337,7 @@ k_charge(int nub, const int32_t *__restrict__ nslots, int nr, int nth, int ld, d
             }
         }
         if (base + k * 256 + tid >= n) cell[k] = -1;
-        // (a row index above 32767 makes the packed cell negative in FP64
-        // only: dead is exactly -1 there, and no cell packs to it)
-        if (F64 ? cell[k] != -1 : cell[k] >= 0) {
+        if (cell_live(cell[k])) {
             const int i = cell_row(cell[k]), j = cell[k] & 0xffff;
             imin = min(imin, i); imax = max(imax, i);
             jmin = min(jmin, j); jmax = max(jmax, j);
@@ -372,7 +370,7 @@ k_charge(int nub, const int32_t *__restrict__ nslots, int nr, int nth, int ld, d
     for (int k = 0; k < kChPPT; k++) {
         const double a = (double)ca[k], b = (double)cb[k];
         const int c = cell[k];
-        bool pend = F64 ? c != -1 : c >= 0;
+        bool pend = cell_live(c);
         const double v00 = Q * (1.0 - a) * (1.0 - b), v10 = Q * a * (1.0 - b);
         const double v01 = Q * (1.0 - a) * b, v11 = Q * a * b;
         // the two values this lane sums (its column), and its neighbour's two

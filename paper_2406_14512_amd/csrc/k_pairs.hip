@@ -54,7 +54,7 @@ __device__ __forceinline__ bool is_parent(void *const *arr, unsigned q, double g
         f64 = us / sqrt(u2);
         return true;
     } else {
-        if (((const int32_t *)arr[0])[q] < 0) return false;
+        if (!cell_live(((const int32_t *)arr[0])[q])) return false;
         const float ur = ((const float *)arr[3])[q], ut = ((const float *)arr[4])[q],
                     up = ((const float *)arr[5])[q];
         const float u2 = ur * ur + ut * ut + up * up;

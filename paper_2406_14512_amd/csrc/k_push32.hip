@@ -358,10 +358,10 @@ __device__ __forceinline__ void push_chunk(KJob A0, const Fields &F, const Patch
             asm volatile("");                  // keeps it a branch
             if (base + (int)q >= n) c = -1;
         }
-        const bool live = PLACE ? c >= 0 && dq >= 0 : c >= 0;
+        const bool live = PLACE ? cell_live(c) && dq >= 0 : cell_live(c);
         // a lane without a particle computes in a cell of the box
         const int cc = live ? c : C.cell0;
-        const int i = cc >> 16, j = cc & 0xffff;
+        const int i = cell_row(cc), j = cc & 0xffff;
         const int ckey = LDS ? (int)mul24(i, (unsigned)acc.TJ) + j : cc;
         bool simple = false;       // stays in its cell: 8 adds at fixed offsets
         bool cross = false;        // leaves its cell: general zigzag
@@ -607,7 +607,7 @@ __device__ __forceinline__ void push_chunk(KJob A0, const Fields &F, const Patch
                 if (LDS) {
                     atomicAdd(&acc.tile[lc + kofs], v);
                 } else {
-                    const int li = (lc >> 16) + kdi, lj = (lc & 0xffff) + kdj;
+                    const int li = cell_row(lc) + kdi, lj = (lc & 0xffff) + kdj;
                     gadd(reinterpret_cast<float *>(reinterpret_cast<char *>(kg) +
                                                    ((mul24(li, acc.ld) + (unsigned)lj) << 2)), v);
                 }
@@ -656,7 +656,7 @@ __device__ __forceinline__ void push_chunk(KJob A0, const Fields &F, const Patch
     if (tid < nq) {
         const float4 r0 = C.queue[2 * tid], r1 = C.queue[2 * tid + 1];
         const int c = __float_as_int(r0.x), dd = __float_as_int(r0.y);
-        zigzag(opaque(A), acc, c >> 16, c & 0xffff, (dd & 3) - 1, ((dd >> 2) & 3) - 1, r0.z, r0.w,
+        zigzag(opaque(A), acc, cell_row(c), c & 0xffff, (dd & 3) - 1, ((dd >> 2) & 3) - 1, r0.z, r0.w,
                r1.x, r1.y, r1.z);
     }
 }
@@ -690,8 +690,8 @@ __device__ __forceinline__ void cell_box(const int32_t *cell, int n, int base, i
 #pragma unroll
         for (int u = 0; u < 4; u++) {
             const int ck = base + (k + u) * kWG + tid < n && k + u < iters ? cb[u] : -1;
-            if (ck >= 0) {
-                const int i = ck >> 16, j = ck & 0xffff;
+            if (cell_live(ck)) {
+                const int i = cell_row(ck), j = ck & 0xffff;
                 imin = min(imin, i); imax = max(imax, i);
                 jmin = min(jmin, j); jmax = max(jmax, j);
             }

@@ -110,13 +110,13 @@ __global__ void k_key32(int nub, const int32_t *__restrict__ nslots, int nth,
     bool killed = false;
     if (q < nslots[0]) {
         int c = CELL[q];
-        if (c >= 0) {
-            int i = c >> 16, j = c & 0xffff;
-            if (kill[(size_t)i * nth + j]) {
+        if (cell_live(c)) {
+            const uint32_t k = cell_key(c, nth);
+            if (kill[k]) {
                 killed = true;
                 CELL[q] = -1;
             } else {
-                key = (uint32_t)i * (uint32_t)nth + (uint32_t)j;
+                key = k;
             }
         }
     }
@@ -680,8 +680,7 @@ __device__ __forceinline__ void place_slot(const ClassView &V, int nth, const ui
         if (FP64) {
             key = keys[q];
         } else {
-            const int cell = (int)v[0];
-            key = (uint32_t)(cell >> 16) * (uint32_t)nth + (uint32_t)(cell & 0xffff);
+            key = cell_key((int)v[0], nth);
         }
         const uint32_t d = stayers_before(V, q) + (uint32_t)mst[key];
 #pragma unroll
@@ -795,9 +794,7 @@ __global__ void __launch_bounds__(256) k_stayer_dest(ClassView V, int nth,
     int32_t ms[kDestSlots];
 #pragma unroll
     for (int k = 0; k < kDestSlots; k++) {
-        uint32_t key = (uint32_t)max(c[k], 0);
-        if (!FP64 && c[k] >= 0)
-            key = (uint32_t)(c[k] >> 16) * (uint32_t)nth + (uint32_t)(c[k] & 0xffff);
+        const uint32_t key = !cell_live(c[k]) ? 0u : FP64 ? (uint32_t)c[k] : cell_key(c[k], nth);
         ms[k] = mst[key];
     }
     int32_t d[kDestSlots];

@@ -223,8 +223,7 @@ __global__ void __launch_bounds__(kBucketThreads) k_bucket_fill(const BucketArgs
             if constexpr (FP64) {
                 key[k] = J.A.keys[q];
             } else {
-                const int c = J.A.cell[q];
-                key[k] = (uint32_t)(c >> 16) * (uint32_t)J.A.nth + (uint32_t)(c & 0xffff);
+                key[k] = cell_key(J.A.cell[q], J.A.nth);
             }
             rank[k] = J.A.rank[q];
         }
@@ -304,8 +303,7 @@ __global__ void __launch_bounds__(256) k_bucket_place(const BucketArgs P) {
         if constexpr (FP64) {
             key = J.A.keys[q];
         } else {
-            const int c = (int)v[k][0];
-            key = (uint32_t)(c >> 16) * (uint32_t)J.A.nth + (uint32_t)(c & 0xffff);
+            key = cell_key((int)v[k][0], J.A.nth);
         }
         const uint32_t d = stay ? stayers_before(V, q) + (uint32_t)J.mst[key]
                                 : mover_place(J, V, key, q);
@@ -337,9 +335,7 @@ __global__ void __launch_bounds__(256) k_bucket_dest(const BucketArgs P) {
         const bool stay = V.smask[q >> 6] & bit, move = V.mmask[q >> 6] & bit;
         int32_t d = -1;
         if (stay || move) {
-            const uint32_t key = FP64 ? (uint32_t)c[k]
-                                      : (uint32_t)(c[k] >> 16) * (uint32_t)J.A.nth +
-                                            (uint32_t)(c[k] & 0xffff);
+            const uint32_t key = FP64 ? (uint32_t)c[k] : cell_key(c[k], J.A.nth);
             d = (int32_t)(stay ? stayers_before(V, q) + (uint32_t)J.mst[key]
                                : mover_place(J, V, key, q));
             if (J.perm) J.perm[d] = q;

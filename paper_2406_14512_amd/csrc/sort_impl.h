@@ -153,8 +153,7 @@ __device__ __forceinline__ void classify_tile(const ClassArgs &A, int tile) {
 #pragma unroll
         for (int k = 0; k < K; k++) {
             const int c = cell[k];
-            const uint32_t kk =
-                c >= 0 ? (uint32_t)(c >> 16) * (uint32_t)A.nth + (uint32_t)(c & 0xffff) : 0u;
+            const uint32_t kk = cell_live(c) ? cell_key(c, A.nth) : 0u;
             key[k] = kk;
             kf[k] = A.kill[kk];
             lo[k] = A.offold[kk];
@@ -163,7 +162,7 @@ __device__ __forceinline__ void classify_tile(const ClassArgs &A, int tile) {
 #pragma unroll
         for (int k = 0; k < K; k++) {
             const int q = base + k * T + tid;
-            const bool live = cell[k] >= 0;
+            const bool live = cell_live(cell[k]);
             const bool killed = live && kf[k] != 0;
             if (killed) A.cell[q] = -1;
             if (!live || killed) key[k] = A.dead;

@@ -64,3 +64,38 @@ def test_fp64_rows_past_32768(nth, n, few):
         assert rel(sim.field(a), ora.field(b)) < 2e-10
     # what the node charges add to the Gauss residual: rho of the particles
     assert rel(sim.field(ffpic.GAUSS), ora.gauss()) < 1e-9
+
+
+@pytest.mark.parametrize("nth,n,few", [(64, 3000, True), (64, 5000, False), (8, 257, False)])
+def test_fp32_rows_past_32768(nth, n, few):
+    """FP32-mixed, whose state holds the packed cell: load, export, the sorts
+    (full, incremental, placed by the push), push, counts and node charges.
+    Offsets carry 6e-8 of a cell, so a particle within 1e-3 of them of an edge
+    may lie on its other side, a radial move (a tenth of a cell) is known to
+    1e-6 and J_r and J_phi to 2e-5; a polar move is 1e-4 of a column, known to
+    1e-3 of itself, and J_theta to 1e-2."""
+    oracle.build(force=False)
+    w, d, p = tall(nth, n, few, nth + n, W.FP32_MIXED)
+    d["sort_interval"] = 1
+    sim, ora = ffpic.Sim(d, capacity=[n]), oracle.Oracle(d)
+    sim.load_particles(0, p)
+    ora.load(0, p)
+    g, o = sim.particles(0), ora.particles(0)
+    assert (o["cell"] // nth >= 32768).sum() > n // 10
+    assert np.array_equal(g["cell"], o["cell"])
+    assert sim.n(0) == n and sim.diagnostics(ffpic.DIAG_MOMENTS)["alive"] == [n]
+    assert rel(sim.field(ffpic.GAUSS), ora.gauss()) < 1e-6
+    sim.run_phases(ffpic.PHASE_PUSH)
+    ora.phases(oracle.PHASE_PUSH)
+    g, o = sim.particles(0), ora.particles(0)
+    assert np.sum(g["cell"] != o["cell"]) <= max(1, 1e-3 * n)
+    currents = [(ffpic.JR, oracle.JR, 2e-5), (ffpic.JPH, oracle.JPH, 2e-5)]
+    if nth > 50:
+        currents.append((ffpic.JTH, oracle.JTH, 1e-2))
+    for a, b, tol in currents:
+        assert rel(sim.field(a), ora.field(b)) < tol
+    sim.step(3)
+    ora.step(3)
+    g, o = sim.particles(0), ora.particles(0)
+    assert sim.diagnostics(ffpic.DIAG_MOMENTS)["alive"] == [n]
+    assert np.sum(np.sort(g["cell"]) != np.sort(o["cell"])) <= max(1, 4e-3 * n)
