@@ -1081,6 +1081,11 @@ int ffpic_load_particles(ffpic_ctx *c, int s, int64_t n, const double *r, const 
         if (!r || !th || !ur || !uth || !uph) throw Fail{FFPIC_EINVAL, "NULL particle array"};
         Species &S = c->sp[s];
         if (S.nub + n > S.cap) throw Fail{FFPIC_ECAPACITY, "species capacity exceeded"};
+        // the append starts at the device's slot count: sorts since the last
+        // load may have lowered it below the host's bound, and the slots
+        // between the two hold stale particles
+        read_words(c, c->nslots + s, sizeof(int32_t));
+        S.nub = (int32_t)c->pin[1];
         const double *src[5] = {r, th, ur, uth, uph};
         double *stage = nullptr;
         if (!on_dev) {

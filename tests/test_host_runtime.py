@@ -1,0 +1,77 @@
+"""The library's host code without a device: a child process runs it on the
+runtime of fake_hip.c (device memory in host memory, kernels that only enter a
+log), so that slot bounds, launch shapes and failure paths can be looked at."""
+import os
+import subprocess
+import sys
+import textwrap
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+
+PRELUDE = """
+import ctypes as C
+import numpy as np
+from paper_2406_14512_amd import ffpic
+from paper_2406_14512_amd import workloads as W
+F = C.CDLL(None)
+F.fake_name.restype = C.c_char_p
+F.fake_grid.restype = C.c_uint32
+F.fake_h2d4.restype = C.POINTER(C.c_int32)
+F.fake_fail.argtypes = [C.c_char_p]
+
+def launches(part):
+    names = [F.fake_name(k).decode() for k in range(F.fake_count())]
+    return [(n, F.fake_grid(k, 0), F.fake_grid(k, 1)) for k, n in enumerate(names) if part in n]
+
+def system(precision, n, cap=None, nth=64, **over):
+    w = W.tiny_dipole(n)
+    w.nr = w.nth = nth
+    d = w.desc()
+    d["precision"] = precision
+    d.update(over)
+    sim = ffpic.Sim(d, capacity=[cap or n] * 2)
+    for s in range(2):
+        sim.load_particles(s, w.particles(s))
+    F.fake_clear()
+    return w, sim
+"""
+
+
+@pytest.fixture(scope="module")
+def fake(tmp_path_factory):
+    from paper_2406_14512_amd import ffpic
+    try:
+        ffpic.lib()
+    except ImportError:
+        from paper_2406_14512_amd import build
+        build.build()
+    so = str(tmp_path_factory.mktemp("fake") / "fake_hip.so")
+    subprocess.run(["gcc", "-O1", "-w", "-shared", "-fPIC", "-o", so,
+                    os.path.join(HERE, "fake_hip.c")], check=True)
+
+    def run(body):
+        env = dict(os.environ, LD_PRELOAD=so, PYTHONPATH=ROOT)
+        env.pop("FFPIC_TUNING_CACHE", None)
+        r = subprocess.run([sys.executable, "-c", PRELUDE + textwrap.dedent(body)], env=env,
+                           cwd=ROOT, capture_output=True, text=True, timeout=120)
+        assert r.returncode == 0, r.stdout + r.stderr
+    return run
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+def test_load_appends_behind_the_devices_count(fake, precision):
+    """A sort on the device lowers its slot count and not the host's bound: a
+    load after it appends at the count, or the slots between the two, which
+    hold stale particles, would be sorted in as live."""
+    fake(f"""
+    w, sim = system({precision}, 100, cap=200)
+    count = F.fake_h2d4()              # of species 1, the last one loaded
+    assert count[0] == 100 and sim.n(1) == 100
+    count[0] = 60                      # forty left, and a sort dropped them
+    p = w.particles(1)
+    sim.load_particles(1, {{k: v[:10] for k, v in p.items()}})
+    assert sim.n(1) == 70, sim.n(1)
+    """)
