@@ -49,6 +49,7 @@ struct P64 {
     const double *rn, *thn;
     double Q, wq, rr;
     double shell_r;        // r below this: only the momentum along B is kept
+    int lds;               // the guesses are within a cell: the LDS patches may serve
 };
 
 struct Push64Args {
@@ -214,9 +215,14 @@ __device__ __forceinline__ double log_cells(KArgs A, Poly64 K, double q) {
     return quot(l, A->p.dlog, A->p.inv_dlog);
 }
 
-// starting cell of a position in single precision; at most one cell off in
-// each direction (the index errors of the float logarithm and products stay
-// below 1e-2 cells up to 65535 cells)
+// Starting cell of a position in single precision.  In theta it is off by the
+// roundings of th, 1 / dth and their product, 3 * 2^-24 of up to 65535 cells or
+// 1.2e-2 cells.  In r those of r / rmin and its logarithm, some 2^-22 together,
+// count 1 / dlog cells each, the products up to 1.2e-2 more: a quarter of a cell
+// at dlog = 2^-20, so there and above at most one cell off in each direction.
+// In thinner shells, or with radii near the ends of the float range, the guess
+// may be any cell, and the LDS patches, sized for one cell off, are not used
+// (P64::lds).
 __device__ __forceinline__ int guess_i(KArgs A, double r) {
     const float g = __logf((float)r * A->p.girm) * A->p.gidl;
     return g > 0.f ? (g < (float)(A->p.nr - 1) ? (int)g : A->p.nr - 1) : 0;
@@ -785,7 +791,7 @@ k_push64(const Push64Jobs) {
     const int TI = i1 - i0 + 4, TJ = j1 - j0 + 4;
     const int fi0 = max(i0 - 1, 0), fj0 = j0 - 1;
     const int TIf = i1 + 1 - fi0 + 1, TJf = j1 - j0 + 3;
-    const bool use_lds = TI * TJ <= kTile64 && TIf * TJf <= kFld64 &&
+    const bool use_lds = p.lds != 0 && TI * TJ <= kTile64 && TIf * TJf <= kFld64 &&
                          TI <= kSide64 && TJ <= kSide64;
     const int r0 = max(i0 - 1, 0), nrow = min(i1 + 2, p.nr) - r0 + 1;
     Counts64 cnt{0, 0, 0};
@@ -870,6 +876,7 @@ static Push64Args push64_job(ffpic_ctx *c, int s) {
     p.wq = c->d.omega_b * qm;
     p.rr = c->d.rr_coef * rr_factor(c) * fabs(qm) * fabs(qm) * fabs(qm);
     p.shell_r = c->d.shell_r;
+    p.lds = c->dlog >= 0x1p-20 && c->d.rmin >= 1e-30 && c->d.rmax <= 1e30;   // see guess_i
     A.nub = (int)S.nub;
     const bool place = c->sort_pending[s];
     A.nslots = place ? (const int32_t *)c->sort_tot[s] : c->nslots + s;
