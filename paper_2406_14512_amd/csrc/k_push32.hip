@@ -73,6 +73,7 @@ struct P32 {
     float aabs;                          // ... at offset aabs
     const float *rn, *sn, *cn;
     float Q, h, kk;                      // charge, dt omega_b qm / 2, dt K_s
+    float weps;                          // 1e-9 of a step, see the move
     int ishell;                          // the shell of kept momentum along B ends in
     float ashell;                        // radial cell ishell at offset ashell
 };
@@ -312,6 +313,7 @@ __device__ __forceinline__ void push_chunk(KJob A0, const Fields &F, const Patch
     const int32_t *dest = PLACE ? A->SP.dest + base : nullptr;
     // the constants of the particle loop
     const float dlog = A->p.dlog, dth = A->p.dth, dt = A->p.dt, h = A->p.h, kk = A->p.kk;
+    const float weps = A->p.weps;
     const float inv_dlog = A->p.inv_dlog, inv_dth = A->p.inv_dth;
     const float Q2 = 0.5f * A->p.Q, Qp4 = 0.25f * A->p.Q / dt;
     const int nth = A->p.nth, iabs = A->p.iabs;
@@ -462,12 +464,14 @@ __device__ __forceinline__ void push_chunk(KJob A0, const Fields &F, const Patch
             // meridional plane, the new one is w2 = sqrt(W^2 + dp^2), and
             // turning into the new plane adds e = w2 - W along the cylindrical
             // radius (formed without cancellation on either side of the axis).
-            // 1e-36 keeps a particle on the axis that does not move finite.
+            // A particle that ends on the axis turns by no azimuth: W is 1e-9
+            // of a step larger, far below the offsets' resolution, so that it
+            // outweighs a dp of zero there; 1.2e-38 keeps the sum from zero.
             const float ivg = frsq(1.f + nr * nr + nt * nt + np * np);   // 1 / gamma
             const float vdt = dt * ivg;
             const float dr = nr * vdt, dtt0 = nt * vdt, dp = np * vdt;
-            const float W = r * st + (dr * st + dtt0 * ct);
-            const float dp2 = dp * dp + 1e-36f;
+            const float W = (r * st + (dr * st + dtt0 * ct)) + weps;
+            const float dp2 = dp * dp + 1.2e-38f;
             const float w22 = W * W + dp2;
             const float iw2 = frsq(w22);
             const float w2 = w22 * iw2, aW = __builtin_fabsf(W);
@@ -956,6 +960,7 @@ PushJob make_push_job(ffpic_ctx *c, int s, int ppt) {
     p.Q = (float)((qm > 0 ? 1.0 : -1.0) * S.weight);
     p.h = (float)(0.5 * c->dt * c->d.omega_b * qm);
     p.kk = (float)(c->dt * c->d.rr_coef * rr_factor(c) * fabs(qm) * fabs(qm) * fabs(qm));
+    p.weps = (float)(1e-9 * c->dt);
     // the shell radius in cell units, split like r_abs
     const bool shell = c->d.shell_r > c->d.rmin;
     const double xs = shell ? log(c->d.shell_r / c->d.rmin) / c->dlog : 0.0;
