@@ -6,10 +6,11 @@
 // This file is compiled without FP contraction, so every operation up to the
 // new state is rounded as written there (a particle's flux is the small
 // difference of two in-cell offsets, so one unit in the last place of a
-// radius shows in it); quotients, roots, the sine, cosine, logarithm and
-// arctangent below are rounded correctly but for rare ties, at a fraction of
-// the library's instructions.  The order in which currents are summed
-// differs.
+// radius shows in it); quotients, roots, the sine, cosine and logarithm below
+// are rounded correctly but for rare ties, the new polar angle but for 2 % of
+// the particles in a coarse grid's first columns and fewer beyond (the device
+// library's arctangent: 25 % anywhere), at a fraction of the library's
+// instructions.  The order in which currents are summed differs.
 //
 // Push (Sect. 3): eq. (motion) integrated with the Boris rotation; the
 // Landau-Lifshitz force g with the effective field of eq. (bperp) is added
@@ -563,18 +564,30 @@ __device__ __forceinline__ void push_chunk64(KArgs A0, const Patch64 &F,
             // errors, so that the sum is rounded as atan2(w, z) of the same
             // arguments almost always.  A move is at most dt <= rmin dth long,
             // so its tangent stays near dth <= 1/16, where the terms left out
-            // are below 1e-18 of it.
+            // are below 1e-18 of it.  That angle carries errors of its own last
+            // place, which the sum drops unless it is itself as small: within
+            // 1/12 of the axis (the first column at least) the angle is that of
+            // (w, z) directly, with the quotient's rounding error.
             double th2;
             if (SERIES) {
-                const double zs = z * st;
-                double cr = __builtin_fma(w, ct, -zs) + __builtin_fma(-z, st, zs);
-                cr += w * ctl - z * stl;
-                const double dot = w * st + z * ct;
-                const double t = quot(cr, dot, rcp64(dot)), t2 = t * t;
-                double T = K[KT];
+                auto series = [&](double t2) {           // 1/3 - t2/5 + t2^2/7 - ...
+                    double T = K[KT];
 #pragma unroll
-                for (int m = 1; m < 7; m++) T = __builtin_fma(-T, t2, K[KT + m]);
-                th2 = fmin(fmax(th + __builtin_fma(-(t * t2), T, t), 0.0), kPi);
+                    for (int m = 1; m < 7; m++) T = __builtin_fma(-T, t2, K[KT + m]);
+                    return T;
+                };
+                if (w < z * (1.0 / 12.0)) {
+                    const double y = rcp64(z), t = quot(w, z, y), t2 = t * t;
+                    const double tl = __builtin_fma(-t, z, w) * y;
+                    th2 = t + __builtin_fma(-(t * t2), series(t2), tl);
+                } else {
+                    const double zs = z * st;
+                    double cr = __builtin_fma(w, ct, -zs) + __builtin_fma(-z, st, zs);
+                    cr += w * ctl - z * stl;
+                    const double dot = w * st + z * ct;
+                    const double t = quot(cr, dot, rcp64(dot)), t2 = t * t;
+                    th2 = fmin(fmax(th + __builtin_fma(-(t * t2), series(t2), t), 0.0), kPi);
+                }
             } else {
                 th2 = atan2(w, z);
             }

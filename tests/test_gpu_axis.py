@@ -49,3 +49,33 @@ def test_momentum_kept_on_landing_on_the_axis(precision, scale, start):
     size = np.sqrt(p["ur"] ** 2 + p["uth"] ** 2 + p["uph"] ** 2)
     # (one cell: the load's sort keeps the order)
     assert np.abs(size / np.hypot(ur, uth) - 1.0).max() < 2e-6
+
+
+@pytest.mark.parametrize("nth", [51, 128, 1024])
+def test_polar_angle_next_to_the_axis(nth):
+    """FP64: the new angle of particles that end in the first column is the
+    rounded angle of the end point, as the oracle's arctangent gives it, however
+    close to the axis they end.  Both round the same end point, so they differ by
+    one unit in the last place at most, but where the sine or cosine of the old
+    angle was rounded differently (a few in a thousand, and the difference grows
+    as the end nears the axis): 99 % within a unit."""
+    oracle.build(force=False)
+    n = 100_000
+    w, d = free(W.FP64, n, nr=nth, nth=nth)
+    g = np.random.Generator(np.random.PCG64(nth))
+    dt, dth = oracle.timestep(d), math.pi / nth
+    th = g.uniform(0.0, min(2.0, 2.0 * dt / (1.1 * dth)) * dth, n)
+    u = g.normal(0.0, 3.0, (3, n))
+    u[2, : n // 2] = 0.0                       # in the meridional plane
+    p = dict(r=np.exp(g.uniform(math.log(1.1), math.log(1.5), n)), th=th, ur=u[0], uth=u[1],
+             uph=u[2])
+    sim, ora = ffpic.Sim(d, capacity=[n]), oracle.Oracle(d)
+    sim.load_particles(0, p)
+    ora.load(0, p)
+    sim.run_phases(ffpic.PHASE_PUSH)
+    ora.phases(oracle.PHASE_PUSH)
+    a, b = sim.particles(0), ora.particles(0)
+    first = (b["r"] > 0) & (b["th"] < dth)
+    units = np.abs(a["th"] - b["th"])[first] / np.spacing(b["th"][first])
+    assert first.sum() > n // 4
+    assert (units > 1.0).mean() < 0.01, (units > 1.0).mean()
