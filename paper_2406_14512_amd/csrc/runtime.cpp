@@ -303,21 +303,33 @@ void upload_background(ffpic_ctx *c) {
     for (int k = 0; k < 3; k++) { rB[k].assign(c->nn, 0.0); rE[k].assign(c->nn, 0.0); }
     auto at = [&](const std::vector<double> &a, int i, int j) { return a[(size_t)i * ld + j]; };
     auto set = [&](std::vector<double> &a, int i, int j, double v) { a[(size_t)i * ld + j] = v; };
+    // rows with a Faraday rate: a circulation that is more than the rounding of
+    // its four terms (in the initial states, which are free of curl, it is up to
+    // 1.3 * 2^-52 of their sum)
+    std::vector<char> rated(nr + 1, 0);
+    auto rate = [&](int i, double circ, double terms) {
+        if (!(std::fabs(circ) <= 0x1p-50 * terms)) rated[i] = 1;
+    };
+    auto mag = [&](const std::vector<double> &a, int i, int j) { return std::fabs(at(a, i, j)); };
     for (int i = 0; i <= nr; i++)
         for (int j = 0; j <= nth; j++) {
             if (j < nth) {
                 double circ = T[T_RN][i] * (T[T_SN][j + 1] * at(E0[2], i, j + 1) - T[T_SN][j] * at(E0[2], i, j));
                 set(rB[0], i, j, -circ / (T[T_RN2][i] * T[T_DCN][j]));
+                rate(i, circ, T[T_RN][i] * (T[T_SN][j + 1] * mag(E0[2], i, j + 1) + T[T_SN][j] * mag(E0[2], i, j)));
             }
             if (i < nr) {
                 if (j > 0 && j < nth) {
                     double circ = T[T_SN][j] * (T[T_RN][i + 1] * at(E0[2], i + 1, j) - T[T_RN][i] * at(E0[2], i, j));
                     set(rB[1], i, j, circ / (T[T_SN][j] * T[T_DR2N][i]));
+                    rate(i, circ, T[T_SN][j] * (T[T_RN][i + 1] * mag(E0[2], i + 1, j) + T[T_RN][i] * mag(E0[2], i, j)));
                 }
                 if (j < nth) {
                     double circ = c->dth * (T[T_RN][i + 1] * at(E0[1], i + 1, j) - T[T_RN][i] * at(E0[1], i, j)) -
                                   T[T_DRN][i] * (at(E0[0], i, j + 1) - at(E0[0], i, j));
                     set(rB[2], i, j, -circ / (c->dth * T[T_DR2N][i]));
+                    rate(i, circ, c->dth * (T[T_RN][i + 1] * mag(E0[1], i + 1, j) + T[T_RN][i] * mag(E0[1], i, j)) +
+                                      T[T_DRN][i] * (mag(E0[0], i, j + 1) + mag(E0[0], i, j)));
                 }
                 double A = T[T_RH2][i] * T[T_DCD][j];
                 double circ = (j < nth ? T[T_RH][i] * T[T_SH][j] * at(B0[2], i, j) : 0.0) -
@@ -362,18 +374,12 @@ void upload_background(ffpic_ctx *c) {
         c->rB0_zero[k] = std::all_of(rB[k].begin(), rB[k].end(),
                                      [&](double v) { return std::fabs(v) <= rb_floor; });
     }
-    // The same row by row: the Faraday rate of a corotating background is zero
-    // but at the outer boundary, where E_theta ends; the rows before the first
-    // with a rate are zero and read as one (see F32Args::rb_row).
-    c->rb_row0 = 0;
-    for (size_t q = 0; c->rb_row0 < nr; c->rb_row0++, q += ld) {
-        bool any = false;
-        for (int k = 0; k < 3 && !any; k++)
-            any = std::any_of(rB[k].begin() + q, rB[k].begin() + q + ld,
-                              [&](double v) { return !(std::fabs(v) <= rb_floor); });
-        if (any) break;
-        for (int k = 0; k < 3; k++) std::fill_n(rB[k].begin() + q, ld, 0.0);
-    }
+    // Row by row, the Faraday rate of a corotating background is zero but at the
+    // outer boundary, where E_theta ends.  The rows before the first with a rate
+    // are zero, and read as one (see F32Args::rb_row); what is dropped there is
+    // the rounding of the background itself.
+    c->rb_row0 = (int)(std::find(rated.begin(), rated.begin() + nr, 1) - rated.begin());
+    for (int k = 0; k < 3; k++) std::fill_n(rB[k].begin(), (size_t)c->rb_row0 * ld, 0.0);
     auto up = [&](void *dst, const std::vector<double> &h) {
         std::vector<float> f(h.begin(), h.end());
         HCHK(hipMemcpy(dst, f.data(), f.size() * sizeof(float), hipMemcpyHostToDevice));
