@@ -7,6 +7,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <exception>
 #include <stdexcept>
 #include <string>
 #include <vector>
@@ -83,6 +84,16 @@ int guarded(ffpic_ctx *c, F &&f) {
         return FFPIC_EHIP;
     }
 }
+
+// A call that queues copies to or from the caller's memory, or its own locals,
+// waits for them on the way out of a failure too: declared after the locals,
+// it drains the stream before they go out of scope.
+struct Drain {
+    ffpic_ctx *c;
+    ~Drain() {
+        if (std::uncaught_exceptions() > 0) (void)hipStreamSynchronize(c->stream);
+    }
+};
 
 void *dmalloc(size_t bytes) {
     void *p = nullptr;
@@ -765,6 +776,7 @@ void run_diagnostics(ffpic_ctx *c, uint32_t what, ffpic_diag *out, double *L, co
     if (flux) poynting(c, b.L);
     unsigned long long rem[FFPIC_MAX_SPECIES * 4];
     double h[kOut];
+    const Drain drain{c};
     HCHK(hipMemcpyAsync(rem, c->removed, sizeof(rem), hipMemcpyDeviceToHost, c->stream));
     HCHK(hipMemcpyAsync(&out->error_word, c->err, sizeof(uint32_t), hipMemcpyDeviceToHost, c->stream));
     HCHK(hipMemcpyAsync(h, b.out, sizeof(h), hipMemcpyDeviceToHost, c->stream));
@@ -1094,6 +1106,8 @@ int ffpic_load_particles(ffpic_ctx *c, int s, int64_t n, const double *r, const 
         S.nub = (int32_t)c->pin[1];
         const double *src[5] = {r, th, ur, uth, uph};
         double *stage = nullptr;
+        int32_t ns = 0, alive = 0;
+        const Drain drain{c};
         if (!on_dev) {
             stage = (double *)dmalloc((size_t)n * 5 * sizeof(double));
             for (int a = 0; a < 5; a++)
@@ -1104,11 +1118,10 @@ int ffpic_load_particles(ffpic_ctx *c, int s, int64_t n, const double *r, const 
         convert_loaded(c, s, S.nub, n, src[0], src[1], src[2], src[3], src[4]);
         S.nub += n;
         c->sort_valid[s] = false;   // appended particles: full sort
-        int32_t ns = (int32_t)S.nub;
+        ns = (int32_t)S.nub;
         HCHK(hipMemcpyAsync(c->nslots + s, &ns, sizeof(ns), hipMemcpyHostToDevice, c->stream));
         const SortItem item{c, s};
         sort_species(&item, 1, c->stream);
-        int32_t alive = 0;
         HCHK(hipMemcpyAsync(&alive, c->nslots + s, sizeof(alive), hipMemcpyDeviceToHost, c->stream));
         HCHK(hipStreamSynchronize(c->stream));
         S.nub = alive;
@@ -1185,6 +1198,7 @@ int ffpic_get_field(ffpic_ctx *c, int comp, double *dst, int on_dev) {
         }
         case FFPIC_DIVB: divb(c, d, nullptr); break;
         }
+        const Drain drain{c};
         if (!on_dev)
             HCHK(hipMemcpyAsync(dst, d, c->nn * sizeof(double), hipMemcpyDeviceToHost, c->stream));
         read_err(c);
@@ -1222,6 +1236,7 @@ int ffpic_get_particles_range(ffpic_ctx *c, int s, int64_t first, int64_t *count
         for (int a = 0; a < 5; a++) o[a] = buf ? buf + (size_t)a * n : (double *)c->sp[s].alt[a];
         export_particles(c, s, first, n, o[0], o[1], o[2], o[3], o[4], oc);
         double *h[5] = {r, th, ur, uth, uph};
+        const Drain drain{c};
         for (int a = 0; a < 5; a++)
             if (h[a]) HCHK(hipMemcpyAsync(h[a], o[a], (size_t)n * sizeof(double), hipMemcpyDeviceToHost, c->stream));
         if (cell) HCHK(hipMemcpyAsync(cell, oc, (size_t)n * sizeof(int32_t), hipMemcpyDeviceToHost, c->stream));
@@ -1295,6 +1310,7 @@ int ffpic_spectra(ffpic_ctx *c, int s, const ffpic_spectra_req *q, double *dN, d
         if (len > c->red_len) throw Fail{FFPIC_EINVAL, "request too large"};
         spectra(c, s, q, c->red);
         std::vector<double> h(len);
+        const Drain drain{c};
         HCHK(hipMemcpyAsync(h.data(), c->red, len * sizeof(double), hipMemcpyDeviceToHost,
                             c->stream));
         HCHK(hipStreamSynchronize(c->stream));
@@ -1365,6 +1381,7 @@ int ffpic_save(ffpic_ctx *c, void *buf, size_t *len) {
         h.step = c->step;
         for (int s = 0; s < FFPIC_MAX_SPECIES; s++) h.nslots[s] = ns[s];
         // all copies are queued, and waited for once
+        const Drain drain{c};
         auto get = [&](void *to, const void *from, size_t n) {
             HCHK(hipMemcpyAsync(to, from, n, hipMemcpyDeviceToHost, c->stream));
         };
@@ -1416,6 +1433,7 @@ int ffpic_restore(ffpic_ctx *c, const void *buf, size_t len) {
         if (len < save_size(c, ns)) throw Fail{FFPIC_EINVAL, "checkpoint truncated"};
         // all copies are queued, in order with the stream's earlier work, and
         // waited for once
+        const Drain drain{c};
         auto put = [&](void *to, const void *from, size_t n) {
             HCHK(hipMemcpyAsync(to, from, n, hipMemcpyHostToDevice, c->stream));
         };

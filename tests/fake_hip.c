@@ -21,11 +21,11 @@ static char fail_on[128];      /* launches of such kernels leave an error */
 static int fail_copy = -1;     /* asynchronous copies until one fails, -1: none */
 static err_t last;
 static int32_t *h2d4;          /* destination of the last 4-byte copy to the device */
-static int nsync;
+static int pending;            /* asynchronous copies since the last wait */
 
-void fake_clear(void) { nlog = 0; nsync = 0; }
+void fake_clear(void) { nlog = 0; }
 int fake_count(void) { return nlog; }
-int fake_syncs(void) { return nsync; }
+int fake_copies_pending(void) { return pending; }
 const char *fake_name(int k) { return names[k]; }
 uint32_t fake_grid(int k, int d) { return d ? grids[k].y : grids[k].x; }
 void fake_fail(const char *sub) { snprintf(fail_on, sizeof fail_on, "%s", sub); }
@@ -68,6 +68,7 @@ err_t hipMemcpyAsync(void *d, const void *s, size_t n, int kind, void *st) {
     if (fail_copy >= 0 && fail_copy-- == 0) return 719;
     if (n == 4 && kind == 1) h2d4 = d;
     memcpy(d, s, n);
+    pending++;
     return 0;
 }
 err_t hipMemset(void *d, int v, size_t n) { memset(d, v, n); return 0; }
@@ -84,7 +85,7 @@ err_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int *n, const void *f, int t,
 static void *handle(void) { return malloc(8); }
 err_t hipStreamCreateWithFlags(void **s, unsigned f) { *s = handle(); return 0; }
 err_t hipStreamDestroy(void *s) { free(s); return 0; }
-err_t hipStreamSynchronize(void *s) { nsync++; return 0; }
+err_t hipStreamSynchronize(void *s) { pending = 0; return 0; }
 err_t hipStreamWaitEvent(void *s, void *e, unsigned f) { return 0; }
 err_t hipStreamBeginCapture(void *s, int m) { return 0; }
 err_t hipStreamEndCapture(void *s, void **g) { *g = handle(); return 0; }

@@ -75,3 +75,33 @@ def test_load_appends_behind_the_devices_count(fake, precision):
     sim.load_particles(1, {{k: v[:10] for k, v in p.items()}})
     assert sim.n(1) == 70, sim.n(1)
     """)
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+def test_failed_copies_are_waited_for(fake, precision):
+    """A call whose k-th queued copy is refused returns the error after waiting
+    for the ones before it, which read or write the caller's memory."""
+    fake(f"""
+    w, sim = system({precision}, 50, cap=100)
+    image = sim.save()
+    p = w.particles(1)
+    calls = dict(
+        save=sim.save, restore=lambda: sim.restore(image), field=lambda: sim.field(ffpic.ER),
+        particles=lambda: sim.particles(0), diagnostics=lambda: sim.diagnostics(poynting=True),
+        load=lambda: sim.load_particles(1, {{k: v[:10] for k, v in p.items()}}))
+    for name, call in calls.items():
+        failed = 0
+        for k in range(100):
+            F.fake_clear()
+            F.fake_fail_copy(k)
+            try:
+                call()
+            except ffpic.FfpicError as e:
+                assert e.code == ffpic.EHIP
+                assert F.fake_copies_pending() == 0, (name, k)
+                failed += 1
+            else:
+                break
+        assert failed >= 2, name
+        F.fake_fail_copy(-1)
+    """)
