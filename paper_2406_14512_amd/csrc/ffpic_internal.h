@@ -73,6 +73,7 @@ struct CycleState {
     int64_t nub[FFPIC_MAX_SPECIES];
     int sort_cur[FFPIC_MAX_SPECIES];
     bool sort_valid[FFPIC_MAX_SPECIES], perm_valid[FFPIC_MAX_SPECIES];
+    bool sort_pending[FFPIC_MAX_SPECIES];   // none between steps
     void *E[3], *B[3], *J[3], *dE[3], *dB[3], *stAlt[6], *Jalt[3];
     int fused_rows, push_ppt;        // settings the launches depend on
     int rates, rb_row0;              // FP32: background rates the field step reads

@@ -625,6 +625,7 @@ CycleState cycle_state(const ffpic_ctx *c) {
         st.sort_cur[s] = c->sort_cur[s];
         st.sort_valid[s] = c->sort_valid[s];
         st.perm_valid[s] = c->perm_valid[s];
+        st.sort_pending[s] = c->sort_pending[s];
     }
     for (int k = 0; k < 3; k++) {
         st.E[k] = c->E[k];
@@ -654,6 +655,7 @@ void set_cycle_state(ffpic_ctx *c, const CycleState &st) {
         c->sort_cur[s] = st.sort_cur[s];
         c->sort_valid[s] = st.sort_valid[s];
         c->perm_valid[s] = st.perm_valid[s];
+        c->sort_pending[s] = st.sort_pending[s];   // a capture may end between sort and push
     }
     for (int k = 0; k < 3; k++) {
         c->E[k] = st.E[k];

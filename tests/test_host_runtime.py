@@ -105,3 +105,53 @@ def test_failed_copies_are_waited_for(fake, precision):
         assert failed >= 2, name
         F.fake_fail_copy(-1)
     """)
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+def test_failed_capture_leaves_no_placement(fake, precision):
+    """A capture that ends between a step's sort and its push never ran: the
+    next push is a plain one, and places by no order."""
+    fake(f"""
+    w, sim = system({precision}, 50)
+    F.fake_fail(b"k_push")
+    try:
+        sim.step(1)
+        assert False
+    except ffpic.FfpicError as e:
+        assert e.code == ffpic.EHIP
+    assert launches("k_bucket_dest"), "the sort left its placement to the push"
+    F.fake_fail(b"")
+    F.fake_clear()
+    sim.run_phases(ffpic.PHASE_PUSH)
+    push = launches("k_push")
+    assert push and all("Lb0EE" in n for n, _, _ in push), push
+    """)
+
+
+@pytest.mark.parametrize("mode,kernel", [(1, "k_push32IL"), (2, "k_push32_group")])
+def test_failed_batch_capture_leaves_no_placement(fake, mode, kernel):
+    fake(f"""
+    w = W.tiny_dipole(50)
+    w.nr = w.nth = 64
+    d = w.desc()
+    d["precision"] = 1
+    b = ffpic.Batch([d, d], [[50, 50]] * 2)
+    for v in b.views:
+        for s in range(2):
+            v.load_particles(s, w.particles(s))
+    b.set_graph({mode})
+    F.fake_clear()
+    F.fake_fail(b"{kernel}")
+    try:
+        b.step(1)
+        assert False
+    except ffpic.FfpicError as e:
+        assert e.code == ffpic.EHIP
+    assert launches("k_bucket_dest") and launches("{kernel}")
+    F.fake_fail(b"")
+    for v in b.views:
+        F.fake_clear()
+        v.run_phases(ffpic.PHASE_PUSH)
+        push = launches("k_push32")
+        assert push and all("Lb0EE" in n for n, _, _ in push), push
+    """)
