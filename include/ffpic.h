@@ -401,12 +401,13 @@ int ffpic_restore(ffpic_ctx *ctx, const void *buf, size_t len);
    Results do not depend on it.  EINVAL for a negative value. */
 int ffpic_set_field_rows(ffpic_ctx *ctx, int32_t rows);
 
-/* Tuning of the FP32 push: particles per thread of a workgroup's chunk, at
-   most (8, 16 or 32; chunks of 256 threads).  Larger chunks share one field
-   and one current patch among more particles; species too small to fill the
-   GPU with them are taken in smaller ones.  Ignored by the FP64 push.  Results do not
-   depend on it beyond the order of floating-point atomic additions.
-   EINVAL for another value. */
+/* Tuning of the FP32 push: particles per thread of a workgroup's chunk (8, 16
+   or 32; chunks of 256 threads).  Larger chunks share one field and one
+   current patch among more particles; smaller ones make more workgroups for
+   small systems.  Until this is called, a context takes 16 (or what
+   ffpic_autotune chose), and fewer for species too small to fill the GPU with
+   them.  Ignored by the FP64 push.  Results do not depend on it beyond the
+   order of floating-point atomic additions.  EINVAL for another value. */
 int ffpic_set_push_chunk(ffpic_ctx *ctx, int32_t ppt);
 
 /* Graph capture of ffpic_step (on by default).  A call of ffpic_step runs
@@ -515,7 +516,9 @@ int ffpic_batch_destroy(ffpic_batch *b);
  * each before trying the next:
  *   1. the sort interval: 8, 4, 16, 2, 32, 1;
  *   2. the field step's slab rows: 0 (automatic), 32, 64, 128, 16;
- *   3. (FP32) the push's particles per thread: 16, 8, 32;
+ *   3. (FP32) the push's particles per thread, at most: 16, 8, 32, leaving out
+ *      those that would launch the same chunks for this context's particles as
+ *      one already timed (a chunk set by ffpic_set_push_chunk is replaced);
  * while the wall time stays within budget_ms (the first candidate of each
  * parameter is always timed).  It then restores the checkpoint and keeps
  * the chosen values.

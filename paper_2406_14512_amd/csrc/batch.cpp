@@ -466,14 +466,18 @@ double time_steps(ffpic_ctx *c, int steps) {
 // the three tuned settings of a context
 struct Setting {
     int interval, rows, ppt;
+    bool fixed;                // the caller's push chunk, not a tuned one
 };
 
-Setting setting_of(const ffpic_ctx *c) { return {c->d.sort_interval, c->fused_rows, c->push_ppt}; }
+Setting setting_of(const ffpic_ctx *c) {
+    return {c->d.sort_interval, c->fused_rows, c->push_ppt, c->push_fixed};
+}
 
 void apply(ffpic_ctx *c, const Setting &v) {
     c->d.sort_interval = v.interval;
     c->fused_rows = v.rows;
     c->push_ppt = v.ppt;
+    c->push_fixed = v.fixed;
 }
 
 void tune_one(ffpic_ctx *c, double budget_ms, ffpic_tuning *out) {
@@ -508,12 +512,23 @@ void tune_one(ffpic_ctx *c, double budget_ms, ffpic_tuning *out) {
         for (const Param &pm : params) {
             double best_ms = 0;
             bool first = true;
+            std::vector<int> chunks;   // of the push candidates timed
             for (int v : pm.values) {
                 if (t.ncand >= FFPIC_TUNE_MAX) break;
                 Setting cand = best;
                 if (pm.kind == FFPIC_TUNE_SORT_INTERVAL) cand.interval = v;
                 if (pm.kind == FFPIC_TUNE_FIELD_ROWS) cand.rows = v;
-                if (pm.kind == FFPIC_TUNE_PUSH_PPT) cand.ppt = v;
+                if (pm.kind == FFPIC_TUNE_PUSH_PPT) {
+                    cand.ppt = v;
+                    cand.fixed = false;
+                    // small species take the same chunk with several settings:
+                    // timing them again would only choose by noise
+                    int64_t slots = 0;
+                    for (int s = 0; s < c->d.nspec; s++) slots += c->sp[s].nub;
+                    const int chunk = ffpic::push_chunk(v, slots);
+                    if (std::find(chunks.begin(), chunks.end(), chunk) != chunks.end()) continue;
+                    chunks.push_back(chunk);
+                }
                 // whole cycles, at least 8 steps
                 const int steps = cand.interval * std::max(1, (8 + cand.interval - 1) / cand.interval);
                 if (!first && elapsed_ms() + last_ms * (steps + cand.interval) * 1.5 > budget_ms)

@@ -113,7 +113,8 @@ struct ffpic_ctx {
     bool rE0_zero[3] = {}, rB0_zero[3] = {};  // FP32: background rate identically zero
     int rb_row0 = 0;                          // FP32: first row with a Faraday rate
     int fused_rows = 0;                       // slab height (0 = from fused_slots)
-    int push_ppt = 16;                        // FP32 push: particles per thread (8, 16, 32)
+    int push_ppt = 16;                        // FP32 push: particles per thread (8, 16, 32), ...
+    bool push_fixed = false;                  // ... at most, or (ffpic_set_push_chunk) exactly
     int fused_slots = 0;                      // workgroups resident on the GPU at once
     // FP32: row / column coefficients of the field step.  FP64 (one allocation,
     // fz_colc): for the push, sines and cosines at multiples of sct_dth with
@@ -294,6 +295,9 @@ void spectra(ffpic_ctx *c, int s, const ffpic_spectra_req *req, double *dev_out)
 // workgroups (grid of them) that take items from the counter pair ctr
 // (zero before the launch, zero again after it).
 size_t push_job_bytes();
+// particles per thread that a launch over this many slots takes with the tuned
+// setting ppt
+int push_chunk(int ppt, int64_t slots);
 // ppt: particles per thread of the grouped push (8, 16, 32), 0 = the
 // context's own setting
 constexpr int kPushKeys = 4;                     // kernel instances of the grouped push

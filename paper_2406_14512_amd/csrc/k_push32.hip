@@ -918,8 +918,8 @@ PushKey push_key(const ffpic_ctx *c, int s) {
 
 int push_key_index(const PushKey &k) { return (k.shell ? 1 : 0) + (k.place ? 2 : 0); }
 
-// Particles per thread of a chunk: the setting (8, 16 or 32), but fewer where
-// the launch's slots would not give every CU its five workgroups, or give them
+// Particles per thread of a chunk where the caller sets none: the tuned number
+// (8, 16 or 32; 16 untuned), but fewer where the launch's slots would not give every CU its five workgroups, or give them
 // in few rounds with a nearly empty last one.  A chunk costs about two rounds
 // of its particles besides (its box and patches), so one per thread pays only
 // while most CUs are idle.  us per launch by particles per thread:
@@ -933,10 +933,13 @@ int push_key_index(const PushKey &k) { return (k.shell ? 1 : 0) + (k.place ? 2 :
 //   2.0e7   509    349    283    268    270
 //   2.8e7  1332    737    508    480    508   (16 systems of a batch)
 //   5.0e7  1199    812    664    616    593
-int push_ppt(int setting, int64_t slots) {
+int push_chunk(int ppt, int64_t slots) {
     const int64_t rounds = slots / kWG;
     const int most = rounds < 1536 ? 1 : rounds < 4096 ? 2 : rounds < 24576 ? 4 : rounds < 131072 ? 8 : 32;
-    return std::min(setting, most);
+    return std::min(ppt, most);
+}
+int push_ppt(const ffpic_ctx *c, int64_t slots) {
+    return c->push_fixed ? c->push_ppt : push_chunk(c->push_ppt, slots);
 }
 
 // the job of one species' push from the context's state, and the host
@@ -1003,7 +1006,7 @@ void push32(ffpic_ctx *c) {
         int64_t slots = 0;
         for (int s = s0; s < c->d.nspec; s++)
             if (!done[s] && c->sort_pending[s] == k.place) slots += c->sp[s].nub;
-        const int ppt = push_ppt(c->push_ppt, slots), chunk = kWG * ppt;
+        const int ppt = push_ppt(c, slots), chunk = kWG * ppt;
         PushJobs P{};
         int m = 0, nb = 0;
         for (int s = s0; s < c->d.nspec; s++) {
@@ -1029,7 +1032,7 @@ int push_group_key(const ffpic_ctx *c, int s) { return push_key_index(push_key(c
 
 int push_job(ffpic_ctx *c, int s, void *out, int ppt, int64_t slots) {
     ffpic::Species &S = c->sp[s];
-    ppt = push_ppt(ppt > 0 ? ppt : c->push_ppt, slots);
+    if (ppt == 0) ppt = push_ppt(c, slots);
     const PushJob J = make_push_job(c, s, ppt);
     std::memcpy(out, &J, sizeof(J));
     after_push(c, s);

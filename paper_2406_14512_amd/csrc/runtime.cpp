@@ -637,7 +637,7 @@ CycleState cycle_state(const ffpic_ctx *c) {
     }
     for (int k = 0; k < 6; k++) st.stAlt[k] = c->stAlt[k];
     st.fused_rows = c->fused_rows;
-    st.push_ppt = c->push_ppt;
+    st.push_ppt = c->push_fixed ? -c->push_ppt : c->push_ppt;
     for (int k = 0; k < 3; k++) st.rates |= (c->rE0_zero[k] ? 0 : 1 << k) | (c->rB0_zero[k] ? 0 : 8 << k);
     st.rb_row0 = c->rb_row0;
     st.record_perm = c->record_perm;
@@ -1491,6 +1491,7 @@ int ffpic_set_push_chunk(ffpic_ctx *c, int32_t ppt) {
         if (ppt != 8 && ppt != 16 && ppt != 32)
             throw Fail{FFPIC_EINVAL, "particles per thread must be 8, 16 or 32"};
         c->push_ppt = ppt;
+        c->push_fixed = true;
     });
 }
 

@@ -155,3 +155,58 @@ def test_failed_batch_capture_leaves_no_placement(fake, mode, kernel):
         push = launches("k_push32")
         assert push and all("Lb0EE" in n for n, _, _ in push), push
     """)
+
+
+def test_push_chunk_setting_is_taken(fake):
+    """ffpic_set_push_chunk gives the particles per thread of every push, also of
+    species that would take fewer without it (one, for 1e5 slots)."""
+    fake("""
+    n = 50_000
+    w, sim = system(1, n)
+    sim.run_phases(ffpic.PHASE_PUSH)
+    assert [g for _, *g in launches("k_push32")] == [[-(-n // 256), 2]]
+    for ppt in (8, 16, 32):
+        sim.set_push_chunk(ppt)
+        F.fake_clear()
+        sim.run_phases(ffpic.PHASE_PUSH)
+        assert [g for _, *g in launches("k_push32")] == [[-(-n // (256 * ppt)), 2]], ppt
+        F.fake_clear()
+        sim.step(1)            # no graph captured with another chunk is replayed
+        assert [g for _, *g in launches("k_push32")] == [[-(-n // (256 * ppt)), 2]], ppt
+    """)
+
+
+def test_grouped_push_chunk_setting_is_taken(fake):
+    fake("""
+    n = 50_000
+    w = W.tiny_dipole(n)
+    w.nr = w.nth = 64
+    d = w.desc()
+    d["precision"] = 1
+    b = ffpic.Batch([d, d], [[n, n]] * 2)
+    for v in b.views:
+        for s in range(2):
+            v.load_particles(s, w.particles(s))
+    b.set_graph(2)
+    items = {0: 4 * -(-n // 256)}
+    items.update({p: 4 * -(-n // (256 * p)) for p in (8, 16, 32)})
+    for ppt in (0, 8, 16, 32):
+        b.set_grouped_chunk(ppt)
+        F.fake_clear()
+        b.step(1)
+        assert [g[0] for _, *g in launches("k_push32_group")] == [min(items[ppt], 1024)], ppt
+    """)
+
+
+def test_tuner_times_only_chunks_that_differ(fake):
+    fake("""
+    w, sim = system(1, 50_000)
+    t = sim.autotune(1e9)
+    assert list(t["timed"]["push_ppt"]) == [16] and t["push_ppt"] == 16, t
+    sim.set_push_chunk(8)
+    t = sim.autotune(1e9)
+    assert list(t["timed"]["push_ppt"]) == [16] and t["push_ppt"] == 16, t
+    F.fake_clear()
+    sim.run_phases(ffpic.PHASE_PUSH)
+    assert [g for _, *g in launches("k_push32")] == [[-(-50_000 // 256), 2]]
+    """)
