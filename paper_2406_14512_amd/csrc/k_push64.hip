@@ -47,7 +47,7 @@ struct P64 {
     float girm, gidl, gidt;     // cell guess: 1 / rmin, 1 / dlog, 1 / dth
     double dsub;                // spacing of the sine and cosine table
     float gids;                 // 1 / dsub, a little less
-    const double *rn, *thn;
+    const double *rn;
     double Q, wq, rr;
     double shell_r;        // r below this: only the momentum along B is kept
     int lds;               // the guesses are within a cell: the LDS patches may serve
@@ -261,7 +261,8 @@ __device__ __forceinline__ double settle_r(KArgs A, Poly64 K, const Rows64 &R, d
     const double a = log_cells<SERIES>(A, K, quot(r, lo.x, lo.y));
     return fmin(fmax(a, 0.0), 1.0);
 }
-// polar cell of th from the cell j (theta_j = j dth, as the table holds it)
+// polar cell of th from the cell j (theta_j = j dth, which the sort's table holds
+// bit for bit, so that both settle the same cell)
 __device__ __forceinline__ double settle_t(KArgs A, double th, int &j) {
     double tlo = j * A->p.dth, thi = (j + 1) * A->p.dth;
     while (j > 0 && th < tlo) { j--; thi = tlo; tlo = j * A->p.dth; }
@@ -883,7 +884,6 @@ static Push64Args push64_job(ffpic_ctx *c, int s) {
     p.dsub = c->sct_dth;
     p.gids = (float)(1.0 / c->sct_dth) * 0.999999f;
     p.rn = c->dtab64[T_RN];
-    p.thn = c->dtab64[T_THN];
     double qm = S.qm;
     p.Q = (qm > 0 ? 1.0 : -1.0) * S.weight;
     p.wq = c->d.omega_b * qm;
