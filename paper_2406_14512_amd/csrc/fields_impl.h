@@ -29,10 +29,12 @@ namespace ffpic {
 // What bounds it: the serial sums, 3.5 us a tile, and beside them the
 // write-back of the other rows, so a CU wants one workgroup with as many rows
 // as the sums hide.  Mask phase of a step, us, against all waves summing,
-// writing and loading in turn: 300 x 517 FP32 14.2 -> 12.4, 1024^2 23.6 -> 19.8,
-// 1500 x 3000 61 -> 46, 2048^2 50 -> 38 (FP64 53 -> 40), 4096^2 118 -> 83 (FP64
-// 124 -> 119), 16 systems grouped 88 -> 63; a single tile, where nothing
-// overlaps, as before (128^2 7.1).
+// writing and loading in turn, in steps of fields alone: 300 x 517 FP32
+// 14.2 -> 12.4, 1024^2 23.6 -> 19.8, 1500 x 3000 61 -> 46, 2048^2 50 -> 38 (FP64
+// 53 -> 40), 4096^2 118 -> 84 (FP64 124 -> 119), 16 systems grouped 88 -> 63; a
+// single tile, where nothing overlaps, as before (128^2 7.1).  After a push of
+// 4e8 particles, which leaves none of B_r in the caches, 4096^2 takes 103 to
+// 111 (FP64 120).
 constexpr int kPsiCols = 256;
 constexpr int kPsiThreads = kPsiCols + 64;   // one per column, and the summing wave
 constexpr int kPsiRun = 32;     // terms a lane sums between LDS reads
@@ -62,7 +64,7 @@ constexpr int kPsiGroupRows = 16;   // 16 systems: 63 us, with 12 rows 77, with 
 // some of them costs more than longer blocks on all: 1024^2 25.2 us with 4 rows
 // and 342 blocks, 19.1 with 6 and 205; 2048^2 FP64 50 with 8 and 293, 40 with
 // 12 and 187; 1281 x 300 11.5 with 8, 13.6 with 12).  Larger grids have several
-// blocks per CU in any case: in FP32 12 rows (4096^2 83 us, with 8 116, with 16
+// blocks per CU in any case: in FP32 12 rows (4096^2 84 us, with 8 116, with 16
 // 146), in FP64 8 (3000 x 1500 41 us, with 12 46 to 56, though 4096^2 119 and
 // 100 to 120).
 inline int psi_rows(int nr, bool fp64) {
@@ -232,7 +234,7 @@ __device__ __forceinline__ void psi_block(const PsiJob<R> &P, int bx, PsiSmem<RO
 }
 
 // (Two workgroups of five waves share a CU up to 128 registers.  FP32 with 12
-// rows fits: 4096^2 83 us, 116 at 129 registers; FP64 would spill four: 2048^2
+// rows fits: 4096^2 84 us, 116 at 129 registers; FP64 would spill four: 2048^2
 // 43 us against 40.)
 template <typename R>
 constexpr int kPsiWaves = std::is_same<R, float>::value ? 4 : 1;

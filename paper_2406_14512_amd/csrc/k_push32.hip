@@ -1,6 +1,7 @@
 // FP32-mixed particle push and charge-conserving deposit.
 //
-// Particle state (SoA, 24 B): cell = (i << 16) | j (int32, -1 = dead slot),
+// Particle state (SoA, 24 B): cell = (i << 16) | j (int32, negative from row
+// 32768 on; -1 = dead slot),
 // a = in-cell offset in log r / dlog, b = in-cell offset in theta / dtheta
 // (FP32, in [0, 1)), u_r, u_theta, u_phi (FP32).  Splitting the position
 // into an integer cell and a small FP32 offset keeps 2^-24 of a cell of
@@ -16,11 +17,13 @@
 // coordinates is ever taken.  Reciprocals and square roots use the
 // hardware approximations (about 1 ulp).
 //
-// What bounds it.  From some 1e8 particles on, HBM: at 2e8 on 4096^2 a launch
-// takes 2.07 ms, 9.6 GB of state (10.8 GB of traffic, 5.2 TB/s) where a copy
-// of them takes 1.93; VALU issue is close behind (350 instructions a
-// particle).  The earlier form (weights and node pairs for the gather,
-// Cartesian move, 456 instructions) took 2.29.  So it is written for few and
+// What bounds it.  From some 1e8 particles on, HBM: the 9.6 GB of state of 2e8
+// particles on 4096^2 (11.3 GB of traffic) take 2.07 ms in the first steps of
+// the sheet and 2.24 some fifty steps on, 5.0 to 5.4 TB/s, where a copy of the
+// state takes 1.93 to 2.01 (4.8 to 5.0 TB/s from box to box); VALU issue is
+// close behind (356 instructions a particle).  The earlier form (weights and
+// node pairs for the gather, Cartesian move, 456 instructions) took 2.29 and
+// 2.58.  So it is written for few and
 // cheap instructions, and waits for nothing it need not: the loads of the
 // next particle, which every lane makes, are waited for without the stores
 // that follow them, index products use 24-bit multiplies, and the cross-lane
@@ -858,8 +861,8 @@ __device__ __forceinline__ void push_block(KJob A0, int chunk, const PushSmem &s
 }
 
 // Five workgroups per CU: LDS and registers (96, some values between the phases
-// spilled) both end there.  2e8 particles: 2.16 ms with four and larger
-// patches, 2.07 with five; six (80 registers) spill in the particle loop.
+// spilled) both end there.  2e8 particles in the sheet's first steps: 2.16 ms
+// with four and larger patches, 2.07 with five; six (80 registers) spill in the particle loop.
 template <bool SHELL, bool PLACE>
 __global__ void __launch_bounds__(kWG) __attribute__((amdgpu_waves_per_eu(5, 8)))
 k_push32(const PushJobs) {

@@ -735,8 +735,8 @@ __device__ __forceinline__ void push_chunk64(KArgs A0, const Patch64 &F,
 // Four waves per SIMD: 128 VGPRs and a quarter of a CU's LDS each.
 //
 // Bound by VALU issue (0.87 of the SIMDs' slots at the 2.0 GHz that FP64
-// work runs at, 889 instructions a particle, two thirds of them FP64).  5e7
-// particles of the 2048^2 sheet: 1.59 ms (2.5 TB/s of its 80 B a particle)
+// work runs at, 896 instructions a particle, two thirds of them FP64).  5e7
+// particles of the 2048^2 sheet: 1.59 to 1.64 ms (2.5 TB/s of its 80 B a particle)
 // against 2.60 ms for one particle per thread with the library's divisions,
 // roots, sine, logarithm and arctangent and the gather from global memory
 // (1751 instructions).  Of the last 0.10 ms, 0.06 came from loading the next
@@ -923,8 +923,8 @@ static Push64Kern push64_kern(int ppt, bool series) {
 }
 
 void push64(ffpic_ctx *c) {
-    // (coarse grids, past the range of the series, take the library's
-    // logarithm and arctangent)
+    // (coarse grids, past the range of the series, take a logarithm of any
+    // argument, log_wide, and the library's arctangent)
     const bool series = c->dlog <= 0.0625 && c->dth <= 0.0625;
     for (int place = 0; place < 2; place++) {
         // the species whose kernel is the same share a launch

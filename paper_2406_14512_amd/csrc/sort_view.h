@@ -41,8 +41,8 @@ __device__ __forceinline__ uint32_t movers_before(const ClassView &V, int x) {
            (uint32_t)__popcll(V.mmask[wd] & below);
 }
 
-// Where a push that also places its species' sort writes each particle
-// (FP32): dest[q] is the place of the particle in slot q in the new order,
+// Where an FP32 push that also places its species' sort writes each particle
+// (the FP64 push takes the places and the second buffer themselves): dest[q] is the place of the particle in slot q in the new order,
 // -1 for a slot that holds none.
 struct SortPlace {
     const int32_t *dest;
